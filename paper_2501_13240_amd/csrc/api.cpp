@@ -223,6 +223,7 @@ static sem_status pmg_prepare(const sem_mesh* m, const double* k, double h2, boo
     L.rho_hat = 1.1 * est;
     L.op64 = op64_of(ml, kl, h2);
     if ((st = op32_of(ml, Wl, kl, h2, s, L.op32))) return st;
+    if (l + 1 == P.lv.size() && (st = prepare_coarse(L.coarse, ml, kl, h2, s))) return st;
     L.dinv64 = Wl.dinv.as<double>();
     L.dinv32 = Wl.dinv32.as<float>();
     bool ok = true;
@@ -1021,6 +1022,9 @@ sem_status sem_setup_pmg(sem_mesh* m, const sem_mesh_desc* desc, const sem_pmg_o
     if (smooths && opts.smoother == SEM_SMOOTH_SCHWARZ &&
         (st = setup_schwarz(L, Nc, E, gid_c.data(), desc->dirichlet ? dir_c.data() : nullptr,
                             xyz_c.data(), s)))
+      return st;
+    if (!smooths && (st = setup_coarse(L.coarse, mc, gid_c.data(),
+                                       desc->dirichlet ? dir_c.data() : nullptr, s)))
       return st;
     std::vector<double> Ik((size_t)(Nc + 1) * (m->N + 1));
     if ((st = host_interp_matrix(m->N, Nc, Ik.data())) || (st = upload(L.Ik64, Ik, s))) return st;

@@ -321,6 +321,9 @@ sem_status vcycle(Pmg& P, int l, const T* r, T* x, const CgScalars* outer, hipSt
   T* wL = local_scratch<T>(m);
   if (!t || !u || !wL) return fail(SEM_ENOMEM, "multigrid work space");
   const bool last = (l + 1 == (int)P.lv.size());
+  if (last && coarse_fits(L.coarse, sizeof(T) == 8))
+    return coarse_cg<T>(L.coarse, m, dinv, r, x, P.coarse_iters, m->nullspace && op.h2 == T(0),
+                        outer, s);
   if (last) {
     T* w = P.vec<T>(L, 4);
     if (!w) return fail(SEM_ENOMEM, "multigrid work space");

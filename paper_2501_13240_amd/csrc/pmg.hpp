@@ -16,6 +16,18 @@
 
 namespace sem {
 
+// The coarsest level's assembled matrix and exchange buffers (coarse.hip)
+constexpr int kCoarseWidth = 27;  // columns of a row: a vertex and its neighbours in 8 hexahedra
+constexpr int kCoarseCus = 256;   // compute units; each holds 3 (FP32) or 2 (FP64) workgroups
+struct CoarseDev {
+  bool on = false;         // the level qualifies (order 1, rows and row lengths within the limits)
+  bool valid = false;      // the matrix of (k == NULL, h2) is there
+  double h2 = 0.0;
+  int nblk = 0;
+  int64_t n_sync = 0;      // 32-bit words of `sync`: exchange slots, then the running tag
+  DevBuf col, cseg, cperm, v64, v32, u, w, zx, sync;
+};
+
 struct PmgLevel {
   sem_mesh* m = nullptr;  // level mesh (level 0: the fine mesh, not owned)
   bool owned = false;
@@ -26,6 +38,7 @@ struct PmgLevel {
   // free vectors of this level: r (input), x (output), t, u, w (scratch),
   // d, rk, q (Chebyshev-Schwarz smoothing)
   DevBuf r64, x64, t64, u64, w64, d64, k64v, q64, r32, x32, t32, u32, w32, d32, k32v, q32;
+  CoarseDev coarse;        // coarsest level only
   SchwarzDev sch;          // Schwarz factors (levels that smooth, Schwarz smoother only)
   double sch_rho = 0.0;    // cached bound of the Schwarz-preconditioned operator (k == NULL)
   double sch_rho_h2 = -1.0;
@@ -68,6 +81,20 @@ template <typename T>
 hipError_t launch_interp(int64_t E, int n_in, int n_out, const T* M, int mode, const T* in,
                          const int32_t* lmap, const int32_t* seg, T* out_L, const int32_t* skip,
                          hipStream_t s);
+
+// host: columns and contribution tables of the coarsest level (`on` stays
+// false when it does not qualify; the cycle then runs cg_fixed_device)
+sem_status setup_coarse(CoarseDev& C, const sem_mesh* m, const int64_t* gid,
+                        const uint8_t* dirichlet, hipStream_t s);
+// per solve: the matrix for (k, h2) and cleared exchange slots
+sem_status prepare_coarse(CoarseDev& C, const sem_mesh* m, const double* k, double h2,
+                          hipStream_t s);
+// the launch fills at most a quarter of the chip (gridsync.hpp)
+bool coarse_fits(const CoarseDev& C, bool f64);
+// `iters` Jacobi-PCG iterations from x = 0 (as cg_fixed_device) in one launch
+template <typename T>
+sem_status coarse_cg(CoarseDev& C, const sem_mesh* m, const T* dinv, const T* b, T* x, int iters,
+                     bool neumann, const CgScalars* outer, hipStream_t s);
 
 // One V-cycle z = V(r) on free vectors of level 0 (Tr: the caller's vector
 // type, Tp: the arithmetic of the cycle).  Coupled to an enclosing flexible CG
