@@ -185,43 +185,6 @@ __global__ __launch_bounds__(Shape<N>::BT) void ax_kernel(
 
 // ------------------------------------------------------------ matrix cores
 
-// One 16-column tile of a contraction along direction DIR of the element
-// block src ([k][j][i], n1 per direction): out[.., row, ..] = sum_l A[row][l]
-// src[.., l, ..], A = D (forward) or D^T (transposed), given as per-lane
-// fragments.  Columns enumerate the two other indices: DIR 0 (along i):
-// col = k n1 + j; DIR 1 (along j): col = k n1 + i; DIR 2 (along k): col =
-// j n1 + i.  ACC adds into dst instead of storing.
-template <int n1, typename T, int DIR, bool ACC>
-__device__ __forceinline__ void contract_tile(const T* __restrict__ src, T* __restrict__ dst,
-                                              const T (&afrag)[(n1 + 3) / 4], int tile, int lane) {
-  constexpr int P2 = n1 * n1, KS = (n1 + 3) / 4;
-  const int col = tile * 16 + (lane & 15);
-  const int kk = lane >> 4;
-  const bool cval = col < P2;
-  const int c1 = cval ? col / n1 : 0, c0 = cval ? col % n1 : 0;
-  typename Mm<T>::V acc = {T(0), T(0), T(0), T(0)};
-#pragma unroll
-  for (int s = 0; s < KS; ++s) {
-    const int l = 4 * s + kk;
-    T b = T(0);
-    if (cval && l < n1) {
-      const int a = DIR == 0 ? c1 * P2 + c0 * n1 + l : DIR == 1 ? c1 * P2 + l * n1 + c0 : l * P2 + col;
-      b = src[a];
-    }
-    acc = Mm<T>::mma(afrag[s], b, acc);
-  }
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int row = Mm<T>::row(lane, r);
-    if (cval && row < n1) {
-      const int a =
-          DIR == 0 ? c1 * P2 + c0 * n1 + row : DIR == 1 ? c1 * P2 + row * n1 + c0 : row * P2 + col;
-      if (ACC) dst[a] += acc[r];
-      else dst[a] = acc[r];
-    }
-  }
-}
-
 typedef _Float16 v4h_t __attribute__((ext_vector_type(4)));
 typedef __bf16 v4bf_t __attribute__((ext_vector_type(4)));
 
@@ -251,9 +214,14 @@ struct Mfma16<2> {
   }
 };
 
-// contract_tile with 16-bit operands: each source value is multiplied by the
-// block scale `sc` (a power of two, exact) before rounding, and each result
-// by `inv` = 1 / sc after accumulation.
+// One 16-column tile of a contraction along direction DIR of the element
+// block src ([k][j][i], n1 per direction): out[.., row, ..] = sum_l A[row][l]
+// src[.., l, ..], A = D (forward) or D^T (transposed), given as this lane's
+// fragment.  Columns enumerate the two other indices: DIR 0 (along i):
+// col = k n1 + j; DIR 1 (along j): col = k n1 + i; DIR 2 (along k): col =
+// j n1 + i.  ACC adds into dst instead of storing.  Each source value is
+// multiplied by the block scale `sc` (a power of two, exact) before rounding,
+// and each result by `inv` = 1 / sc after accumulation.
 template <int n1, int LP, int DIR, bool ACC>
 __device__ __forceinline__ void contract_tile16(const float* __restrict__ src,
                                                 float* __restrict__ dst,
@@ -307,85 +275,309 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
+// Shape of the 16-bit operand kernel
 template <int N>
 struct MShape {
   static constexpr int n1 = N + 1;
   static constexpr int P2 = n1 * n1;
   static constexpr int P = P2 * n1;
-  // threads per element (= per workgroup).  N = 9 (1000 points) takes 256
-  // threads with four points each rather than 512 with two: as many waves
-  // per CU hold more elements (FP32: 7 instead of 4, FP64: 4 instead of 3),
-  // stand-alone apply 241 -> 221 us (FP32) and 395 -> 385 us (FP64) on the
-  // 32^3 cube.  N = 10 keeps 512 (six points per thread would cost registers).
+  // threads per element (= per workgroup)
   static constexpr int TPB =
       P <= 64 ? 64 : P <= 128 ? 128 : P <= 1000 ? 256 : 512;
   static constexpr int PPT = (P + TPB - 1) / TPB;    // points per thread
   static constexpr int NT = (P2 + 15) / 16;          // 16-column tiles per direction
-  static constexpr int KS = (n1 + 3) / 4;            // K steps of 4
   static constexpr int NW = TPB / 64;                // wavefronts
 };
 
-// Operator with matrix-core contractions, one element per workgroup.
-// Phases: loads -> forward contractions (3 NT tiles over the wavefronts) ->
-// pointwise metric and k -> transposed contractions accumulated direction
-// by direction into the (now free) input block -> stores.
-// LP = 0: contractions in T (FP64 or FP32 MFMA).  LP = 1 / 2 (T = float):
-// bfloat16 / half operands for D, the u block and each v_a block, FP32
-// accumulation; for half each block is scaled by its power-of-two block
-// scale, whose maxima are reduced before the barriers the phases already have.
+// -------------------------------------- matrix-core operator (FP64, FP32)
+
+// Wavefronts per element and waves per SIMD (register budget) by order and
+// bytes of T.  The waves are the most that do not spill (a spill of ten
+// registers costs 40-80 % here: N = 9 FP64 at five waves 173 us against 97 at
+// three), few wavefronts of several points each beat many of one (N = 5: one
+// wavefront per element 87 us, four 122 us), and with the budget stated the
+// results of the products stay out of the accumulation registers, from which
+// each would be moved.
+constexpr int ax_waves(int N, int bytes) {
+  return N == 5 ? 1 : N == 6 ? (bytes == 8 ? 2 : 3) : N == 10 ? 8 : 4;
+}
+constexpr int ax_min_waves(int N, int bytes) {
+  return bytes == 8 ? (N == 5 || N == 9 ? 3 : N == 7 ? 6 : 4)
+                    : (N == 5 || N == 9 ? 5 : N == 6 || N == 7 ? 8 : 7);
+}
+// Shape of the operator kernel: NW wavefronts per element, each lane with the
+// points t, t + 64 NW, ... (coalesced factor loads at every order).
+template <int N, typename T>
+struct LShape {
+  static constexpr int n1 = N + 1;
+  static constexpr int P2 = n1 * n1;
+  static constexpr int P = P2 * n1;
+  static constexpr int NW = ax_waves(N, sizeof(T));
+  static constexpr int TPB = 64 * NW;
+  static constexpr int PPT = (P + TPB - 1) / TPB;    // points per lane
+  static constexpr int NT = (P2 + 15) / 16;          // 16-column tiles per direction
+  static constexpr int TPW = (NT + NW - 1) / NW;     // tiles per wavefront and direction
+  static constexpr int KS = (n1 + 3) / 4;            // products per tile
+  static constexpr int LS = n1 == 8 ? 9 : n1;        // LDS row stride (n1 = 8: 16 rows of 8
+                                                     // would meet in a quarter of the banks)
+  static constexpr int PS = n1 * LS;                 // LDS layer stride
+};
+
+// LDS place of point q of the element
+template <int N, typename T>
+__device__ __forceinline__ int lds_point(int q) {
+  using S = LShape<N, T>;
+  return S::LS == S::n1 ? q : (q / S::n1) * S::LS + q % S::n1;
+}
+
+// Fragments of D (forward) and D^T: the row of a product's result register r
+// in lane group kk is kk + 4 r in both precisions (FP32 results come in rows
+// 4 kk + r, so the rows of its operand are taken in that order; every lane
+// then has KS result rows), and step s contracts the columns kk + 4 s.
+template <int N, typename T>
+__device__ __forceinline__ void d_frags(const T* __restrict__ D, int lane,
+                                        T (&af)[LShape<N, T>::KS], T (&at)[LShape<N, T>::KS]) {
+  constexpr int n1 = N + 1;
+  const int i = lane & 15, kk = lane >> 4;
+  const int row = sizeof(T) == 8 ? i : (i >> 2) + 4 * (i & 3), rc = min(row, n1 - 1);
+#pragma unroll
+  for (int s = 0; s < LShape<N, T>::KS; ++s) {
+    const int l = 4 * s + kk, lc = min(l, n1 - 1);
+    const T f = D[rc * n1 + lc], t = D[lc * n1 + rc];
+    const bool ok = row < n1 && l < n1;
+    af[s] = ok ? f : T(0);
+    at[s] = ok ? t : T(0);
+  }
+}
+
+// The three contractions of one 16-column tile: along i from si, along j
+// from sj, along k from sk (element blocks in LDS), results to ri, rj, rk at
+// the same lines (in place allowed).  No access but the last rows' stores is
+// predicated: columns past the last one repeat it (the same values to the same
+// places) and contraction indices past n1 repeat the last one against zero
+// fragments.
+template <int N, typename T>
+__device__ __forceinline__ void contract_tile(int tile, int lane, const T (&m)[LShape<N, T>::KS],
+                                              const T* si, const T* sj, const T* sk, T* ri,
+                                              T* rj, T* rk) {
+  using S = LShape<N, T>;
+  constexpr int n1 = S::n1, KS = S::KS, LS = S::LS, PS = S::PS;
+  const int kk = lane >> 4;
+  const int col = min(tile * 16 + (lane & 15), S::P2 - 1);
+  const int cq = col / n1, cr = col % n1;
+  const int bi = cq * PS + cr * LS, bj = cq * PS + cr, bk = cq * LS + cr;
+  T xi[KS], xj[KS], xk[KS];
+#pragma unroll
+  for (int s = 0; s < KS; ++s) {
+    const int l = 4 * s + 3 < n1 ? kk + 4 * s : min(kk + 4 * s, n1 - 1);
+    xi[s] = si[bi + l];
+    xj[s] = sj[bj + l * LS];
+    xk[s] = sk[bk + l * PS];
+  }
+  typename Mm<T>::V ai = {T(0), T(0), T(0), T(0)}, aj = ai, ak = ai;
+#pragma unroll
+  for (int s = 0; s < KS; ++s) {
+    ai = Mm<T>::mma(m[s], xi[s], ai);
+    aj = Mm<T>::mma(m[s], xj[s], aj);
+    ak = Mm<T>::mma(m[s], xk[s], ak);
+  }
+#pragma unroll
+  for (int r = 0; r < KS; ++r) {
+    const int row = kk + 4 * r;
+    if (4 * r + 3 < n1 || row < n1) {
+      ri[bi + row] = ai[r];
+      rj[bj + row * LS] = aj[r];
+      rk[bk + row * PS] = ak[r];
+    }
+  }
+}
+
+// Operator with matrix-core contractions in T, one element per workgroup:
+//   loads, u to LDS | D along i, j, k | metric and k | D^T along i, j, k, in
+//   place | sum of the three, store                          (| = barrier).
+// Bound by its stream: 64 B per point in FP64, 32 B in FP32 (+ 4 B of routing
+// codes and the gathers in the solve).  Measured on boxes of 8 million points,
+// us per apply, against the form whose tile accesses each sat behind a branch
+// and whose three transposed contractions ran one after another:
+//   N           5        6        7        8        9       10
+//   FP64    122->88  105->94   83->82  118->92  116->97  106->97
+//   FP32     84->58   76->53   53->43   63->48   59->51   62->50
+// (A form that kept each wavefront's points in the products' result layout, so
+// that the k contractions need no LDS, loads the factors in runs of 16: as fast
+// at N = 7, 158 us at N = 8.)
+//
 // MODE 0: u and w local [E][P].  MODE 1: u gathered from a free vector
 // through lmap.  MODE 2 (in-solve split): lmap holds v >= 0 for a free node v
 // with one local copy, -(v + 2) for a shared free node v, -1 for a Dirichlet
 // copy; single-copy results go straight to the free vector wf[v], shared
-// copies' results to w (local, for the segmented sum), and epart[2 (NW e +
-// wave) + a] receives each wavefront's sums of p w and of w over all its
-// free copies (p = the gathered input; over the copies of a shared node
-// they add up to p_g w_g and w_g), reduced in a fixed order.  MODE 3: MODE 2
-// with nontemporal shared-copy stores (for local arrays larger than the
-// memory-side cache).  MODE 4 / 5: MODE 2 / 3 without the wavefront sums (a
-// Chebyshev pass needs none).  MODE 6 / 7: MODE 2 / 3 with p w only (sum(w)
-// serves the null-space projection alone).  Each sum costs the kernel more
-// than its instructions suggest (measured per launch, N = 9 FP64: no sums
-// 375 us, p w 390 us, three sums 440-460 us; N = 7 FP64: 89, 92, 95 us).
-// Waves per SIMD the split in-solve form asks for: the gather form's
-// occupancy at N = 6 and N = 9, which a few extra registers would cost it
-// (at N = 9, with 512-thread workgroups, one fewer resident workgroup per CU
-// once made the kernel 1.8x slower).
-constexpr int split_min_waves(int N) { return N == 6 ? 7 : N == 9 ? 4 : 1; }
-
-template <int N, typename T, int MODE, int LP>
-__global__ __launch_bounds__(MShape<N>::TPB) __attribute__((
-    amdgpu_waves_per_eu(MODE >= 2 && sizeof(T) == 8 ? split_min_waves(N) : 1))) void ax_mfma_kernel(
-    const T* __restrict__ u, const int32_t* __restrict__ lmap, T* __restrict__ w,
-    const T* __restrict__ kf, const T h2, const T* __restrict__ G, const T* __restrict__ B,
-    const T* __restrict__ D, const int64_t E, const int32_t* __restrict__ skip,
-    T* __restrict__ wf, double* __restrict__ epart) {
-  using S = MShape<N>;
-  constexpr int n1 = S::n1, P = S::P, TPB = S::TPB, PPT = S::PPT, NT = S::NT, KS = S::KS,
-                NW = S::NW;
-  static_assert(LP == 0 || std::is_same<T, float>::value, "16-bit operands need FP32 data");
-  // wavefront sums into epart: 2 (p w, w) or 1 (p w)
+// copies' results to w (local, at the element's surface slots, for the
+// segmented sum), and epart[2 (NW e + wave) + a] receives each wavefront's sums
+// of p w and of w over all its free copies (p = the gathered input; over the
+// copies of a shared node they add up to p_g w_g and w_g), reduced in a fixed
+// order.  MODE 3: MODE 2 with nontemporal shared-copy stores (for local arrays
+// larger than the memory-side cache).  MODE 4 / 5: MODE 2 / 3 without the
+// wavefront sums (a Chebyshev pass needs none).  MODE 6 / 7: MODE 2 / 3 with
+// p w only (sum(w) serves the null-space projection alone).
+template <int N, typename T, int MODE>
+__global__ __launch_bounds__((LShape<N, T>::TPB))
+    __attribute__((amdgpu_waves_per_eu(ax_min_waves(N, sizeof(T))))) void ax_line_kernel(
+        const T* __restrict__ u, const int32_t* __restrict__ lmap, T* __restrict__ w,
+        const T* __restrict__ kf, const T h2, const T* __restrict__ G, const T* __restrict__ B,
+        const T* __restrict__ D, const int32_t* __restrict__ skip, T* __restrict__ wf,
+        double* __restrict__ epart) {
+  using S = LShape<N, T>;
+  constexpr int n1 = S::n1, P = S::P, KS = S::KS, PPT = S::PPT, TPB = S::TPB, NW = S::NW,
+                NT = S::NT, TPW = S::TPW, SZ = n1 * S::PS;
   constexpr int kSums = (MODE == 2 || MODE == 3) ? 2 : (MODE == 6 || MODE == 7) ? 1 : 0;
-  constexpr bool kDots = kSums > 0;
-  constexpr bool kNtShared = (MODE == 3 || MODE == 5 || MODE == 7);  // nontemporal shared-copy stores
-  constexpr bool kScale = LP == 2;
+  constexpr bool kNtShared = (MODE == 3 || MODE == 5 || MODE == 7);
   if (skip && *skip) return;  // uniform over the grid
-  __shared__ T su[P];
-  __shared__ T sa[3][P];
-  __shared__ float smax[4][NW];  // block maxima of u, v_r, v_s, v_t per wavefront (LP = 2)
-  T* so = su;  // output accumulator, reuses the input block after the forward phase
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  __shared__ T su[SZ];
+  __shared__ T sa[3][SZ];
+  const int t = threadIdx.x, lane = t & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
   const int64_t e = blockIdx.x;
   const bool use_k = kf != nullptr;
   const bool use_h2 = h2 != T(0);
-  (void)E;
+  const T* Ge = G + e * 6 * P;
+  const int64_t eP = e * P;
+  // point s of this lane (past the element's last: the last one again)
+  auto point = [&](int s) -> uint32_t {
+    return (s + 1) * TPB <= P ? t + s * TPB : min(t + s * TPB, P - 1);
+  };
+  auto in_element = [&](int s) { return (s + 1) * TPB <= P || t + s * TPB < P; };
 
-  T uq[PPT], gq[PPT][6], kq[PPT];
-  // MODE 2: each point's routing code, kept in LDS until the stores (in
-  // registers it cost the N = 9 kernel a wave per SIMD)
-  __shared__ int32_t scode[MODE >= 2 ? P : 1];
-  // MODE >= 1: every routing code of this thread first, then the gathers
-  // through them (0.6 % faster in-solve and p-multigrid iterations)
+  // all of the element's loads are issued before the first use: routing codes
+  // first, the factors before the gathers that wait for the codes
+  T uq[PPT], gq[PPT][6], kq[PPT], bq[PPT];
+  int32_t code[PPT];
+  (void)code;
+  if constexpr (MODE >= 1) {
+#pragma unroll
+    for (int s = 0; s < PPT; ++s) code[s] = ld_stream(lmap + eP + point(s));
+  }
+#pragma unroll
+  for (int s = 0; s < PPT; ++s) {
+    const uint32_t q = point(s);
+    if constexpr (MODE == 0) uq[s] = ld_stream(u + eP + q);
+#pragma unroll
+    for (int c = 0; c < 6; ++c) gq[s][c] = ld_stream(Ge + c * P + q);
+    kq[s] = use_k ? ld_stream(kf + eP + q) : T(1);
+    bq[s] = use_h2 ? ld_stream(B + eP + q) : T(0);
+  }
+  T af[KS], at[KS];
+  d_frags<N, T>(D, lane, af, at);
+  if constexpr (MODE >= 1) {
+#pragma unroll
+    for (int s = 0; s < PPT; ++s) {
+      const int32_t cd = code[s];
+      const int32_t g = MODE >= 2 ? (cd >= 0 ? cd : cd <= -2 ? -(cd + 2) : -1) : cd;
+      const T v = u[max(g, 0)];
+      uq[s] = g >= 0 ? v : T(0);
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < PPT; ++s) su[lds_point<N, T>(point(s))] = uq[s];
+  __syncthreads();
+#pragma unroll
+  for (int x = 0; x < TPW; ++x) {
+    const int tile = wv + x * NW;
+    if ((x + 1) * NW <= NT || tile < NT)
+      contract_tile<N, T>(tile, lane, af, su, su, su, sa[0], sa[1], sa[2]);
+  }
+  __syncthreads();
+  // metric and k
+#pragma unroll
+  for (int s = 0; s < PPT; ++s) {
+    const int q = lds_point<N, T>(point(s));
+    const T ur = sa[0][q], us = sa[1][q], ut = sa[2][q];
+    const T* gc = gq[s];
+    T vr = gc[0] * ur + gc[1] * us + gc[2] * ut;
+    T vs = gc[1] * ur + gc[3] * us + gc[4] * ut;
+    T vt = gc[2] * ur + gc[4] * us + gc[5] * ut;
+    if (use_k) {
+      vr *= kq[s];
+      vs *= kq[s];
+      vt *= kq[s];
+    }
+    if (in_element(s)) {
+      sa[0][q] = vr;
+      sa[1][q] = vs;
+      sa[2][q] = vt;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int x = 0; x < TPW; ++x) {
+    const int tile = wv + x * NW;
+    if ((x + 1) * NW <= NT || tile < NT)
+      contract_tile<N, T>(tile, lane, at, sa[0], sa[1], sa[2], sa[0], sa[1], sa[2]);
+  }
+  __syncthreads();
+  double ps[2] = {0.0, 0.0};
+  (void)ps;
+#pragma unroll
+  for (int s = 0; s < PPT; ++s) {
+    const int q = (int)point(s), ql = lds_point<N, T>(q);
+    T acc = (sa[0][ql] + sa[1][ql]) + sa[2][ql];
+    if (use_h2) acc += h2 * bq[s] * uq[s];
+    if (!in_element(s)) continue;
+    if constexpr (MODE >= 2) {
+      const int32_t cd = code[s];
+      if (cd >= 0) {
+        st_stream(acc, wf + cd);
+      } else if (cd <= -2) {
+        // shared copy: at its surface slot of the element's block
+        T* dst = w + eP + surface_rank(q % n1, (q / n1) % n1, q / (n1 * n1), N);
+        if constexpr (kNtShared)
+          st_stream(acc, dst);
+        else
+          *dst = acc;
+      }
+      if constexpr (kSums > 0) {
+        if (cd != -1) {  // free copies only
+          ps[0] += (double)uq[s] * (double)acc;
+          if constexpr (kSums == 2) ps[1] += (double)acc;
+        }
+      }
+    } else {
+      st_stream(acc, w + eP + q);
+    }
+  }
+  // the sums of one wavefront: no barrier, no LDS
+#pragma unroll
+  for (int a = 0; a < kSums; ++a) {
+    const double x = wave_sum_d(ps[a]);
+    if (lane == 0) epart[(e * NW + wv) * 2 + a] = x;
+  }
+}
+
+// The same operator with 16-bit contraction operands (FP32 data): D, the u
+// block and each v_a block rounded to bfloat16 (LP = 1) or IEEE half (LP = 2;
+// each block scaled by its power-of-two block scale, whose maxima are reduced
+// before the barriers the phases already have), FP32 accumulation.  MODE 0: u
+// and w local; MODE 1: u gathered from a free vector through lmap.  Phases:
+// loads -> forward contractions (3 NT tiles over the wavefronts) -> pointwise
+// metric and k -> transposed contractions accumulated direction by direction
+// into the (now free) input block -> stores.
+template <int N, int MODE, int LP>
+__global__ __launch_bounds__(MShape<N>::TPB) void ax_mfma16_kernel(
+    const float* __restrict__ u, const int32_t* __restrict__ lmap, float* __restrict__ w,
+    const float* __restrict__ kf, const float h2, const float* __restrict__ G,
+    const float* __restrict__ B, const float* __restrict__ D, const int32_t* __restrict__ skip) {
+  using S = MShape<N>;
+  constexpr int n1 = S::n1, P = S::P, TPB = S::TPB, PPT = S::PPT, NT = S::NT, NW = S::NW;
+  constexpr bool kScale = LP == 2;
+  if (skip && *skip) return;  // uniform over the grid
+  __shared__ float su[P];
+  __shared__ float sa[3][P];
+  __shared__ float smax[4][NW];  // block maxima of u, v_r, v_s, v_t per wavefront (LP = 2)
+  float* so = su;  // output accumulator, reuses the input block after the forward phase
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int64_t e = blockIdx.x;
+  const bool use_k = kf != nullptr;
+  const bool use_h2 = h2 != 0.0f;
+
+  float uq[PPT], gq[PPT][6], kq[PPT];
   int32_t lvq[PPT];
   (void)lvq;
   if constexpr (MODE >= 1) {
@@ -395,65 +587,43 @@ __global__ __launch_bounds__(MShape<N>::TPB) __attribute__((
       lvq[s] = ld_stream(lmap + e * P + (qr < P ? qr : P - 1));
     }
   }
-  // the geometric factors (and k) are requested before the first routing
-  // code is used, so the bulk of the stream does not wait for the codes
 #pragma unroll
   for (int s = 0; s < PPT; ++s) {
     const int qr = t + s * TPB;
     const int q = qr < P ? qr : P - 1;
-    const int64_t idx = e * P + q;
-    const T* g = G + e * 6 * P + q;
+    const float* g = G + e * 6 * P + q;
 #pragma unroll
     for (int c = 0; c < 6; ++c) gq[s][c] = ld_stream(g + c * P);
-    kq[s] = use_k ? ld_stream(kf + idx) : T(1);
+    kq[s] = use_k ? ld_stream(kf + e * P + q) : 1.0f;
   }
 #pragma unroll
   for (int s = 0; s < PPT; ++s) {
     const int qr = t + s * TPB;
     const int q = qr < P ? qr : P - 1;
-    const int64_t idx = e * P + q;
     if constexpr (MODE >= 1) {
-      const int32_t lv = lvq[s];
-      const int32_t lm = MODE >= 2 ? (lv >= 0 ? lv : lv <= -2 ? -(lv + 2) : -1) : lv;
-      if constexpr (MODE >= 2)
-        if (qr < P) scode[qr] = lv;
-      const T v = u[lm >= 0 ? lm : 0];
-      uq[s] = lm >= 0 ? v : T(0);
+      const int32_t lm = lvq[s];
+      const float v = u[lm >= 0 ? lm : 0];
+      uq[s] = lm >= 0 ? v : 0.0f;
     } else {
-      uq[s] = ld_stream(u + idx);
+      uq[s] = ld_stream(u + e * P + q);
     }
   }
   // derivative-matrix fragments: forward A = D, transposed A = D^T
-  T af[KS], at[KS];
-  typename Mfma16<LP == 0 ? 1 : LP>::V af16, at16;
+  typename Mfma16<LP>::V af16, at16;
   {
     const int row = lane & 15, kk = lane >> 4;
-    if constexpr (LP == 0) {
 #pragma unroll
-      for (int s = 0; s < KS; ++s) {
-        const int l = 4 * s + kk;
-        const bool ok = row < n1 && l < n1;
-        af[s] = ok ? D[row * n1 + l] : T(0);
-        at[s] = ok ? D[l * n1 + row] : T(0);
-      }
-    } else {
-#pragma unroll
-      for (int x = 0; x < 4; ++x) {
-        const int l = 4 * kk + x;
-        const bool ok = row < n1 && l < n1;
-        af16[x] = Mfma16<LP>::cvt(ok ? D[row * n1 + l] : 0.0f);
-        at16[x] = Mfma16<LP>::cvt(ok ? D[l * n1 + row] : 0.0f);
-      }
+    for (int x = 0; x < 4; ++x) {
+      const int l = 4 * kk + x;
+      const bool ok = row < n1 && l < n1;
+      af16[x] = Mfma16<LP>::cvt(ok ? D[row * n1 + l] : 0.0f);
+      at16[x] = Mfma16<LP>::cvt(ok ? D[l * n1 + row] : 0.0f);
     }
   }
-  (void)af;
-  (void)at;
-  (void)af16;
-  (void)at16;
   if constexpr (kScale) {
     float mu = 0.0f;
 #pragma unroll
-    for (int s = 0; s < PPT; ++s) mu = fmaxf(mu, fabsf((float)uq[s]));
+    for (int s = 0; s < PPT; ++s) mu = fmaxf(mu, fabsf(uq[s]));
     mu = wave_max(mu);
     if (lane == 0) smax[0][wv] = mu;
   }
@@ -463,14 +633,7 @@ __global__ __launch_bounds__(MShape<N>::TPB) __attribute__((
     if (q < P) su[q] = uq[s];
   }
   __syncthreads();
-  if constexpr (LP == 0) {
-    for (int job = wv; job < 3 * NT; job += NW) {
-      const int dir = job / NT, tile = job - dir * NT;
-      if (dir == 0) contract_tile<n1, T, 0, false>(su, sa[0], af, tile, lane);
-      else if (dir == 1) contract_tile<n1, T, 1, false>(su, sa[1], af, tile, lane);
-      else contract_tile<n1, T, 2, false>(su, sa[2], af, tile, lane);
-    }
-  } else {
+  {
     float sc = 1.0f;
     if constexpr (kScale) {
       float m = 0.0f;
@@ -492,11 +655,11 @@ __global__ __launch_bounds__(MShape<N>::TPB) __attribute__((
   for (int s = 0; s < PPT; ++s) {
     const int q = t + s * TPB;
     if (q < P) {
-      const T ur = sa[0][q], us = sa[1][q], ut = sa[2][q];
-      const T* gc = gq[s];
-      T vr = gc[0] * ur + gc[1] * us + gc[2] * ut;
-      T vs = gc[1] * ur + gc[3] * us + gc[4] * ut;
-      T vt = gc[2] * ur + gc[4] * us + gc[5] * ut;
+      const float ur = sa[0][q], us = sa[1][q], ut = sa[2][q];
+      const float* gc = gq[s];
+      float vr = gc[0] * ur + gc[1] * us + gc[2] * ut;
+      float vs = gc[1] * ur + gc[3] * us + gc[4] * ut;
+      float vt = gc[2] * ur + gc[4] * us + gc[5] * ut;
       if (use_k) {
         vr *= kq[s];
         vs *= kq[s];
@@ -506,9 +669,9 @@ __global__ __launch_bounds__(MShape<N>::TPB) __attribute__((
       sa[1][q] = vs;
       sa[2][q] = vt;
       if constexpr (kScale) {
-        mv[0] = fmaxf(mv[0], fabsf((float)vr));
-        mv[1] = fmaxf(mv[1], fabsf((float)vs));
-        mv[2] = fmaxf(mv[2], fabsf((float)vt));
+        mv[0] = fmaxf(mv[0], fabsf(vr));
+        mv[1] = fmaxf(mv[1], fabsf(vs));
+        mv[2] = fmaxf(mv[2], fabsf(vt));
       }
     }
   }
@@ -520,13 +683,7 @@ __global__ __launch_bounds__(MShape<N>::TPB) __attribute__((
     }
   }
   __syncthreads();
-  if constexpr (LP == 0) {
-    for (int tile = wv; tile < NT; tile += NW) contract_tile<n1, T, 0, false>(sa[0], so, at, tile, lane);
-    __syncthreads();
-    for (int tile = wv; tile < NT; tile += NW) contract_tile<n1, T, 1, true>(sa[1], so, at, tile, lane);
-    __syncthreads();
-    for (int tile = wv; tile < NT; tile += NW) contract_tile<n1, T, 2, true>(sa[2], so, at, tile, lane);
-  } else {
+  {
     float sc[3] = {1.0f, 1.0f, 1.0f};
     if constexpr (kScale) {
 #pragma unroll
@@ -547,50 +704,13 @@ __global__ __launch_bounds__(MShape<N>::TPB) __attribute__((
       contract_tile16<n1, LP, 2, true>(sa[2], so, at16, tile, lane, sc[2], 1.0f / sc[2]);
   }
   __syncthreads();
-  double ps[2] = {0.0, 0.0};
-  (void)ps;
 #pragma unroll
   for (int s = 0; s < PPT; ++s) {
     const int q = t + s * TPB;
     if (q < P) {
-      const int64_t idx = e * P + q;
-      T acc = so[q];
-      if (use_h2) acc += h2 * ld_stream(B + idx) * uq[s];
-      if constexpr (MODE >= 2) {
-        const int32_t c = scode[q];
-        if (c >= 0) {
-          st_stream(acc, wf + c);
-        } else if (c <= -2) {
-          // shared copy: at its surface slot of the element's block
-          T* dst = w + e * P + surface_rank(q % n1, (q / n1) % n1, q / (n1 * n1), N);
-          if constexpr (kNtShared)
-            st_stream(acc, dst);
-          else
-            *dst = acc;
-        }
-        if constexpr (kDots) {
-          if (c != -1) {  // free copies only
-            ps[0] += (double)uq[s] * (double)acc;
-            if constexpr (kSums == 2) ps[1] += (double)acc;
-          }
-        }
-      } else {
-        st_stream(acc, w + idx);
-      }
-    }
-  }
-  if constexpr (kDots) {
-    // the sums of one wavefront: no barrier, no LDS.  Lane 0 is found by
-    // mbcnt here rather than from the lane index computed at the start,
-    // which the compiler would otherwise keep (and at N = 9 spill) all along.
-    // (Tried and not kept: the sums on the matrix cores, 16 instead of 30
-    // vector instructions per sum, and the three DPP chains interleaved:
-    // both as slow or slower.)
-    const bool first_lane = __builtin_amdgcn_mbcnt_lo(~0u, 0u) == 0;
-#pragma unroll
-    for (int a = 0; a < kSums; ++a) {
-      const double x = wave_sum_d(ps[a]);
-      if (first_lane) epart[(e * NW + wv) * 2 + a] = x;
+      float acc = so[q];
+      if (use_h2) acc += h2 * ld_stream(B + e * P + q) * uq[s];
+      st_stream(acc, w + e * P + q);
     }
   }
 }
@@ -697,17 +817,31 @@ __global__ void mass_kernel(int64_t n, const T* __restrict__ B, const T* __restr
       hipLaunchKernelGGL(kernel, grid, block, 0, stream, __VA_ARGS__);                 \
   } while (0)
 
-template <int N, typename T, int LP>
-hipError_t run_ax_mfma(const sem_mesh* m, const T* u, const int32_t* lmap, T* w, const T* k, T h2,
+template <int N, int LP>
+hipError_t run_ax_mfma16(const sem_mesh* m, const float* u, const int32_t* lmap, float* w,
+                         const float* k, float h2, const float* G, const float* B, const float* D,
+                         hipStream_t s, const int32_t* skip, hipEvent_t ev0, hipEvent_t ev1) {
+  const dim3 grid((unsigned)m->E), block(MShape<N>::TPB);
+  if (lmap)
+    SEM_LAUNCH(ev0, ev1, (ax_mfma16_kernel<N, 1, LP>), grid, block, s, u, lmap, w, k, h2, G, B, D,
+               skip);
+  else
+    SEM_LAUNCH(ev0, ev1, (ax_mfma16_kernel<N, 0, LP>), grid, block, s, u, lmap, w, k, h2, G, B, D,
+               skip);
+  return hipGetLastError();
+}
+
+template <int N, typename T>
+hipError_t run_ax_line(const sem_mesh* m, const T* u, const int32_t* lmap, T* w, const T* k, T h2,
                        const T* G, const T* B, const T* D, hipStream_t s, const int32_t* skip,
                        hipEvent_t ev0, hipEvent_t ev1) {
-  using M = MShape<N>;
+  const dim3 grid((unsigned)m->E), block(LShape<N, T>::TPB);
   if (lmap)
-    SEM_LAUNCH(ev0, ev1, (ax_mfma_kernel<N, T, 1, LP>), dim3((unsigned)m->E), dim3(M::TPB), s, u,
-               lmap, w, k, h2, G, B, D, m->E, skip, (T*)nullptr, (double*)nullptr);
+    SEM_LAUNCH(ev0, ev1, (ax_line_kernel<N, T, 1>), grid, block, s, u, lmap, w, k, h2, G, B, D,
+               skip, (T*)nullptr, (double*)nullptr);
   else
-    SEM_LAUNCH(ev0, ev1, (ax_mfma_kernel<N, T, 0, LP>), dim3((unsigned)m->E), dim3(M::TPB), s, u,
-               lmap, w, k, h2, G, B, D, m->E, skip, (T*)nullptr, (double*)nullptr);
+    SEM_LAUNCH(ev0, ev1, (ax_line_kernel<N, T, 0>), grid, block, s, u, lmap, w, k, h2, G, B, D,
+               skip, (T*)nullptr, (double*)nullptr);
   return hipGetLastError();
 }
 
@@ -716,15 +850,15 @@ hipError_t run_ax(const sem_mesh* m, const T* u, const int32_t* lmap, T* w, cons
                   const T* G, const T* B, const T* D, hipStream_t s, const int32_t* skip, int lp,
                   hipEvent_t ev0, hipEvent_t ev1) {
   if constexpr (std::is_same<T, float>::value) {
-    if (lp == 1) return run_ax_mfma<N, float, 1>(m, u, lmap, w, k, h2, G, B, D, s, skip, ev0, ev1);
-    if (lp == 2) return run_ax_mfma<N, float, 2>(m, u, lmap, w, k, h2, G, B, D, s, skip, ev0, ev1);
+    if (lp == 1) return run_ax_mfma16<N, 1>(m, u, lmap, w, k, h2, G, B, D, s, skip, ev0, ev1);
+    if (lp == 2) return run_ax_mfma16<N, 2>(m, u, lmap, w, k, h2, G, B, D, s, skip, ev0, ev1);
   }
   if (lp != 0) return hipErrorInvalidValue;
   if constexpr (has_mfma(N)) {
     const AxChoice c = ax_choice();
     const bool mfma = c == AxChoice::Auto ? prefer_mfma(N, lmap != nullptr, sizeof(T) == 4)
                                           : c == AxChoice::Mfma;
-    if (mfma) return run_ax_mfma<N, T, 0>(m, u, lmap, w, k, h2, G, B, D, s, skip, ev0, ev1);
+    if (mfma) return run_ax_line<N, T>(m, u, lmap, w, k, h2, G, B, D, s, skip, ev0, ev1);
   }
   using S = Shape<N>;
   const int64_t grid = (m->E + S::EPB - 1) / S::EPB;
@@ -782,7 +916,6 @@ hipError_t run_ax_split(const sem_mesh* m, const T* u, T* wf, T* wL, double* epa
                         const T* k, T h2, const T* G, const T* B, const T* D, hipStream_t s,
                         const int32_t* skip, hipEvent_t ev0, hipEvent_t ev1) {
   if constexpr (has_mfma(N)) {
-    using M = MShape<N>;
     // shared-copy results stay in the memory-side cache for the segmented
     // sum when the local array fits well inside it (256 MB): plain stores up
     // to m->ax_nt_bytes, 128 MB by default (the 32x32x16, N = 7 box: 67 MB,
@@ -793,12 +926,12 @@ hipError_t run_ax_split(const sem_mesh* m, const T* u, T* wf, T* wL, double* epa
     // none without epart (MODE 4 / 5).
     const bool plain = m->nL * (int64_t)sizeof(T) <= m->ax_nt_bytes;
     const int mode = !epart ? (plain ? 4 : 5) : mean_sums ? (plain ? 2 : 3) : (plain ? 6 : 7);
-    const dim3 grid((unsigned)m->E), block(M::TPB);
+    const dim3 grid((unsigned)m->E), block(LShape<N, T>::TPB);
     const int32_t* lm = m->lmap2.as<int32_t>();
 #define SEM_SPLIT_CASE(MD)                                                                   \
   case MD:                                                                                   \
-    SEM_LAUNCH(ev0, ev1, (ax_mfma_kernel<N, T, MD, 0>), grid, block, s, u, lm, wL, k, h2, G, B, \
-               D, m->E, skip, wf, epart);                                                    \
+    SEM_LAUNCH(ev0, ev1, (ax_line_kernel<N, T, MD>), grid, block, s, u, lm, wL, k, h2, G, B, D,  \
+               skip, wf, epart);                                                    \
     break;
     switch (mode) {
       SEM_SPLIT_CASE(2)
@@ -816,17 +949,7 @@ hipError_t run_ax_split(const sem_mesh* m, const T* u, T* wf, T* wL, double* epa
 }
 }  // namespace
 
-int ax_split_parts(int N) {
-  switch (N) {
-    case 5: return MShape<5>::NW;
-    case 6: return MShape<6>::NW;
-    case 7: return MShape<7>::NW;
-    case 8: return MShape<8>::NW;
-    case 9: return MShape<9>::NW;
-    case 10: return MShape<10>::NW;
-    default: return 0;
-  }
-}
+int ax_split_parts(int N, bool f64) { return has_mfma(N) ? ax_waves(N, f64 ? 8 : 4) : 0; }
 
 bool ax_split_available(const sem_mesh* m) {
   // SEM_AX_SPLIT=0 (read once) keeps the gather form in the solve

@@ -1196,7 +1196,7 @@ sem_status cg_solve(const sem_mesh* m, SolveWork& W, const CgArgs<T, Tp>& a, CgR
   double* partC = part + 2 * kReduceBlocks * kMaxReduce;
   // single-copy free nodes leave the operator directly (see launch_ax_split)
   const bool split = op_it.lp == 0 && ax_split_available(m);
-  const int64_t nparts = split ? m->E * ax_split_parts(m->N) : 0;
+  const int64_t nparts = split ? m->E * ax_split_parts(m->N, sizeof(T) == 8) : 0;
   double* epart = split ? W.vec<double>(W.epart, 2 * nparts) : nullptr;
   if (split && !epart) return fail(SEM_ENOMEM, "work space");
   // Chebyshev fused into the iteration's kernels (needs the split operator)
