@@ -13,6 +13,7 @@ namespace sem {
 struct AdvRule {
   int q1 = 0;             // points per direction
   DevBuf mats64, mats32;  // J [q1][n], JD = J D [q1][n], J^T [n][q1]
+  DevBuf eo64, eo32;      // 3/2 rule: even and odd halves of J, JD and J^T (see Eo)
   DevBuf G64, G32;        // [E][9][q1^3]: w detJ dr_a/dx_d in slot 3 a + d
 };
 
@@ -33,9 +34,9 @@ hipError_t launch_adv_geometry(const sem_mesh* m, int q1, const double* mats, co
 
 // out[k][e] = C_e(u) f[k] for every element and each of nf fields: u DEVICE
 // [3][E][P], f and out [nf][E][P]; rule 0 reads D (DEVICE [n][n]) and G
-// [E][9][P], rule 1 mats and G [E][9][q1^3]
+// [E][9][P], rule 1 eo and G [E][9][q1^3]
 template <typename T>
-hipError_t launch_advect(const sem_mesh* m, int rule, int nf, const T* mats, const T* D,
+hipError_t launch_advect(const sem_mesh* m, int rule, int nf, const T* eo, const T* D,
                          const T* G, const T* u, const T* f, T* out, hipStream_t s);
 
 }  // namespace sem

@@ -1145,7 +1145,23 @@ sem_status sem_setup_advection(sem_mesh* m, const sem_mesh_desc* desc, int32_t r
   std::vector<float> mats32(mats.begin(), mats.end());
   std::unique_ptr<AdvRule> R(new AdvRule());
   R->q1 = q1;
+  // even and odd halves (A_ij +- A_i,NI-1-j) / 2 of the first half of the rows
+  // (with the middle one) of J, JD and J^T, row by row
+  std::vector<double> eo;
+  auto halves = [&](const double* A, int no, int ni) {
+    for (int i = 0; i < (no + 1) / 2; ++i)
+      for (int sign = 1; sign >= -1; sign -= 2)
+        for (int j = 0; j < (sign > 0 ? (ni + 1) / 2 : ni / 2); ++j) {
+          const double a = A[i * ni + j], b = A[i * ni + ni - 1 - j];
+          eo.push_back(2 * j + 1 == ni ? a : 0.5 * (a + sign * b));
+        }
+  };
+  halves(mats.data(), q1, n);
+  halves(JD, q1, n);
+  halves(JT, n, q1);
+  const std::vector<float> eo32(eo.begin(), eo.end());
   if ((st = upload(R->mats64, mats, s)) || (st = upload(R->mats32, mats32, s)) ||
+      (st = upload(R->eo64, eo, s)) || (st = upload(R->eo32, eo32, s)) ||
       (st = R->G64.ensure((size_t)m->E * 9 * Q * sizeof(double))) ||
       (st = R->G32.ensure((size_t)m->E * 9 * Q * sizeof(float))))
     return st;
@@ -1204,11 +1220,11 @@ sem_status sem_advect_fields(const sem_mesh* m, int32_t rule, const void* u, int
   hipStream_t s = (hipStream_t)stream;
   hipError_t e;
   if (prec == SEM_FP64)
-    e = launch_advect<double>(m, rule, nf, R->mats64.as<double>(), m->D64.as<double>(),
+    e = launch_advect<double>(m, rule, nf, R->eo64.as<double>(), m->D64.as<double>(),
                               R->G64.as<double>(), (const double*)u, (const double*)f,
                               (double*)out, s);
   else
-    e = launch_advect<float>(m, rule, nf, R->mats32.as<float>(), m->D32.as<float>(),
+    e = launch_advect<float>(m, rule, nf, R->eo32.as<float>(), m->D32.as<float>(),
                              R->G32.as<float>(), (const float*)u, (const float*)f, (float*)out,
                              s);
   if (e != hipSuccess) return hip_fail(e, "advect");

@@ -1,8 +1,7 @@
 // Convective term C_e(u) f on every element (the advection terms of the
 // Boussinesq equations, Sec. 4.1).
 //
-// Over-integrated rule (M = floor(3(N+1)/2) Gauss points per direction), one
-// element at a time per workgroup of four wavefronts:
+// Over-integrated rule (M = floor(3(N+1)/2) Gauss points per direction):
 //   1. each velocity component u_d is interpolated to the M^3 points,
 //      (J x J x J) u_d, and folded into V_a = sum_d G_ad u_d (a = r, s, t);
 //      the nine factors G_ad = w detJ dr_a/dx_d are streamed from HBM once;
@@ -10,20 +9,13 @@
 //      (J x JD x J) f and (JD x J x J) f with JD = J D, give
 //      c = sum_a V_a df/dr_a;
 //   3. the test functions project back: out = (J^T x J^T x J^T) c.
-// Every 1-D interpolation is a batch of 16-column tiles of a 16x16x4 MFMA
-// product (the M x (N+1) matrix J fits one tile, N <= 10), staged through
-// LDS; the last interpolation stage (along t) keeps its tile in registers,
-// where V and c are formed, so no M^3 array of u or of the derivatives is
-// ever stored.  The factors (9 M^3 values against 5 (N+1)^3 of fields) are
-// most of the HBM traffic.  With one field the kernel reaches about half of
-// the HBM peak: the factors of a pass can be requested only one pass ahead
-// within the register budget, less than the loaded latency.  With several
-// fields sharing V most of the work is MFMA products and LDS stages, at about
-// a third of the matrix cores' peak (the stages' barrier and LDS latencies,
-// at two workgroups per CU).
+// The factors at the set-up come from the same stages of the coordinates, as
+// batches of 16-column tiles of 16x16x4 MFMA products.
 //
 // Collocation (the GLL nodes themselves): one thread per node, derivative
 // sums over LDS.
+#include <type_traits>
+
 #include "advection.hpp"
 #include "mfma_16x16x4.hpp"
 
@@ -91,17 +83,13 @@ constexpr int kAdvWaves = 4;
 constexpr int kAdvThreads = 64 * kAdvWaves;
 
 // The interpolation stages of an order-N element to M points per direction.
-template <int N, int M, typename T, int W = kAdvWaves>
+template <int N, int M, typename T>
 struct Stages {
   static constexpr int n = N + 1, P = n * n * n, Q = M * M * M;
   typedef Ct<T, n, n, n, M, 0> I0;  // (n,n,n) -> (n,n,M)
   typedef Ct<T, n, n, M, M, 1> I1;  // (n,n,M) -> (n,M,M)
   typedef Ct<T, n, M, M, M, 2> I2;  // (n,M,M) -> (M,M,M)
-  typedef Ct<T, M, M, M, n, 2> B2;  // (M,M,M) -> (n,M,M)
-  typedef Ct<T, n, M, M, n, 1> B1;  // (n,M,M) -> (n,n,M)
-  typedef Ct<T, n, n, M, n, 0> B0;  // (n,n,M) -> (n,n,n)
-  static constexpr int KN = I0::KS, KM = B2::KS;
-  static constexpr int TPW = (I2::NT + W - 1) / W;  // last-stage tiles per wave
+  static constexpr int KN = I0::KS;
   // LDS: the input block and the two first-stage outputs (later the M^3
   // array c and the (n,n,M) back-projection stage), and one (n,M,M) array
   static constexpr int IX = P + 2 * n * n * M;
@@ -109,199 +97,284 @@ struct Stages {
   static_assert(Q <= IX && P <= YS, "LDS regions");
 };
 
-// Tiles of a stage handled by this wavefront (t = wv, wv + kW, ...), unrolled.
-#define FOR_TILES(C, ...)                                                               \
-  _Pragma("unroll") for (int ti_ = 0; ti_ < (C::NT + kW - 1) / kW; ++ti_) {           \
-    const int t = wv + ti_ * kW;                                                        \
-    if (t < C::NT) { __VA_ARGS__; }                                                     \
-  }
+// ------------------------------------------------- the over-integrated rule
 
-// Wavefronts per workgroup of the dealiased kernel: the faster of four and
-// eight, measured per order and precision on meshes of 14-16 thousand
-// elements.  Eight halve each wave's last-stage tiles, and with them its V
-// accumulators and prefetched factors: FP64 from N = 8 on then runs two waves
-// per SIMD instead of one (1.3-1.6x faster at N = 8..10), FP64 at N = 5, 6
-// gains 13-20 % and FP32 at N = 6 8 %.  FP64 at N = 7 and FP32 at the other
-// orders are faster with four waves, which keep two workgroups per CU; at
-// N <= 4 the stages have too few tiles for eight waves.
-template <int N, typename T>
-constexpr int adv_waves() {
-  return (sizeof(T) == 8 ? (N == 5 || N == 6 || N >= 8) : N == 6) ? 8 : kAdvWaves;
-}
-
-// Persistent: workgroup b processes elements b, b + grid, ...  The factors a
-// pass consumes are requested one pass ahead (the first pass's during the
-// previous element's field passes and projections), into the registers the
-// previous pass has just consumed, so the factor stream stays in flight
-// while the matrix cores interpolate.  V is formed once per element and
-// applied to each of the nf fields f[k] (stride E P, like u).
-template <int N, typename T>
-__global__ __launch_bounds__((64 * adv_waves<N, T>())) void adv_dealias_kernel(
-    int64_t E, int nf, const T* __restrict__ mats, const T* __restrict__ G,
-    const T* __restrict__ u, int64_t ustride, const T* __restrict__ f, T* __restrict__ out) {
-  constexpr int M = (3 * (N + 1)) / 2;
-  constexpr int kW = adv_waves<N, T>(), kThreads = 64 * kW;
-  typedef Stages<N, M, T, kW> S;
-  typedef typename S::I0 I0;
-  typedef typename S::I1 I1;
-  typedef typename S::I2 I2;
-  typedef typename S::B2 B2;
-  typedef typename S::B1 B1;
-  typedef typename S::B0 B0;
-  typedef typename Mm<T>::V V;
-  constexpr int n = S::n, P = S::P, Q = S::Q, TPW = S::TPW;
-  // the four input blocks and the first-stage outputs; later c and the
-  // (n,n,M) projection stage
-  constexpr int R0 = 4 * P + 2 * n * n * M;
-  static_assert(Q <= R0, "c fits the first region");
-  // FP64: the f pass forms its three (n,M,M) arrays in one phase when they
-  // fit beside the rest with two workgroups per CU (two barriers per field
-  // instead of six; measured 3.5 % faster with four fields at N = 7).  FP32
-  // keeps one array: the larger LDS and register footprint cost it a wave
-  // per SIMD (27 % slower)
-  constexpr bool kMerge = sizeof(T) == 8 && (R0 + 3 * S::YS) * sizeof(T) <= 80 * 1024;
-  __shared__ T sR[R0];
-  __shared__ T sY[kMerge ? 3 * S::YS : S::YS];
-  T* sIn = sR;  // u_x, u_y, u_z, f
-  T* sX0 = sR + 4 * P;
-  T* sX1 = sX0 + n * n * M;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  T aJ[S::KN], aJD[S::KN], aJT[S::KM];
-  fragments<T, M, n>(mats, aJ, lane);
-  fragments<T, M, n>(mats + M * n, aJD, lane);
-  fragments<T, n, M>(mats + 2 * M * n, aJT, lane);
-  // this lane's point in each of its last-stage tiles (-1: none)
-  int goff[TPW][4];
+// One 1-D transform y = A x of a line held in registers, A (NO x NI) with
+// A[NO-1-i][NI-1-j] = A[i][j] (interpolation, projection) or = -A[i][j] (ANTI,
+// differentiation, whose rows also sum to zero): the mirror symmetry of the
+// nodes.  With the even and odd parts e_j = x_j + x_{NI-1-j}, o_j = x_j -
+// x_{NI-1-j}, half of the outputs are a + b and the mirrored ones a - b (ANTI:
+// b - a), a = ce e, b = co o: 68 operations for 8 -> 12 points instead of 96.
+// ANTI takes the e_j less the innermost one, so a constant line gives exact
+// zeros and one product per output goes.
+//
+// The coefficients, row by row (HI of ce, NI / 2 of co), are uniform over the
+// wavefront and come through scalar registers, which cannot hold a matrix:
+// each chunk of rows is requested while the one before it is used (left to the
+// compiler's order, which waits for each: four FP64 fields on the 32x32x16, N =
+// 7 box 1081 against 640 us).
+template <int NI, int NO, bool ANTI, typename T>
+struct Eo {
+  static constexpr int HI = (NI + 1) / 2, NH = NI / 2, HO = (NO + 1) / 2, SZ = HO * NI;
+  static constexpr int kRow = NI * (int)sizeof(T) / 4;            // scalar registers per row
+  // rows per chunk: about 32 registers; single rows measured faster at rows of
+  // 12 and 18 (four FP64 fields: N = 5 361 -> 318 us, N = 8 379 -> 331 us, where
+  // N = 7 and N = 9 lose 8-11 % by them)
+  static constexpr int RC = kRow >= 24 || kRow == 12 || kRow == 18 ? 1 : kRow >= 12 ? 2 : 4;
+  static constexpr int NC = (HO + RC - 1) / RC;
+  T e[HI], o[NH == 0 ? 1 : NH];
+  template <typename F>
+  __device__ __forceinline__ explicit Eo(F&& x) {
 #pragma unroll
-  for (int ti = 0; ti < TPW; ++ti) {
-    const int t = wv + ti * kW;
-    const int col = t * 16 + (lane & 15);
+    for (int j = 0; j < NH; ++j) {
+      const T p = x(j), q = x(NI - 1 - j);
+      e[j] = p + q;
+      o[j] = p - q;
+    }
+    if constexpr (NI & 1) e[NH] = x(NH);
+    if constexpr (ANTI) {
+      const T c = (NI & 1) ? e[NH] + e[NH] : e[HI - 1];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int row = Mm<T>::row(lane, r);
-      goff[ti][r] = (t < I2::NT && row < M && col < M * M) ? row * M * M + col : -1;
+      for (int j = 0; j < HI - 1; ++j) e[j] -= c;
     }
   }
-  T g[TPW][3][4];  // G_ad of pass d at those points
-  auto fetch = [&](int64_t ee, int d) {
-    const T* Gd = G + (ee * 9 + d) * Q;
+  template <typename F>
+  __device__ __forceinline__ void apply(const T* __restrict__ coef, F&& put) const {
+    typedef const T __attribute__((address_space(4))) * Uniform;  // read by scalar loads
+    int anew = 0;
+    asm volatile("" : "+s"(anew));  // for every line: the reads are not kept over the kernel
+    Uniform c = (Uniform)(uintptr_t)coef + anew;
+    T buf[2][RC * NI];
+    auto fetch = [&](int k) {
 #pragma unroll
-    for (int ti = 0; ti < TPW; ++ti)
+      for (int x = 0; x < RC * NI; ++x)
+        if (k * RC * NI + x < SZ) buf[k & 1][x] = c[k * RC * NI + x];
+    };
+    fetch(0);
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
+    for (int k = 0; k < NC; ++k) {
+      if (k + 1 < NC) fetch(k + 1);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int a = 0; a < 3; ++a)
-          g[ti][a][r] = goff[ti][r] >= 0 ? Gd[3 * a * Q + goff[ti][r]] : T(0);
+      for (int r = 0; r < RC; ++r) {
+        const int i = k * RC + r;
+        if (i >= HO) break;
+        const T* row = buf[k & 1] + r * NI;
+        constexpr int ne = ANTI ? HI - 1 : HI;
+        const bool mid = (NO & 1) && i == HO - 1;
+        T a = T(0), b = T(0);
+        if (!(mid && ANTI))
+#pragma unroll
+          for (int j = 0; j < ne; ++j) a = j == 0 ? row[j] * e[j] : a + row[j] * e[j];
+        if (!(mid && !ANTI))
+#pragma unroll
+          for (int j = 0; j < NH; ++j) b = j == 0 ? row[HI + j] * o[j] : b + row[HI + j] * o[j];
+        if (mid) {
+          put(i, ANTI ? b : a);
+        } else {
+          put(i, a + b);
+          put(NO - 1 - i, ANTI ? b - a : a - b);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+};
+
+// Shape of the dealiased kernel: n nodes and M points per direction.
+template <int N, typename T>
+struct AdvShape {
+  static constexpr int n = N + 1, M = (3 * n) / 2, P = n * n * n, Q = M * M * M;
+  static constexpr int n2 = n * n, nM = n * M, M2 = M * M;
+  static constexpr int TPB = ((M2 + 63) / 64) * 64;
+  // LDS rows (k, jq) of n or M values along i, an odd number apart (a line per
+  // lane then meets every bank)
+  static constexpr int SA = n | 1, SY = M | 1;
+  static constexpr int A = nM * SA, Y = nM * SY;
+  // three line arrays at once (u components, derivative directions) up to 40
+  // KB, else one after another, with more barriers and more workgroups per CU
+  // (four fields, FP64: N = 6, 30 KB, 364 against 402 us; N = 7, 51 KB, 399
+  // against 363 us)
+  static constexpr int NY = (3 * A + 3 * Y) * (int)sizeof(T) <= 40 * 1024 ? 3 : 1;
+  static constexpr int NA = NY == 3 ? 3 : 2;
+  typedef Eo<n, M, false, T> J;
+  typedef Eo<n, M, true, T> JD;
+  typedef Eo<M, n, false, T> JT;
+  static_assert(2 * A >= Y && 3 * n2 <= 3 * TPB, "regions");
+};
+
+// Over-integrated rule, one element per workgroup; a thread transforms one
+// line at a time in registers:
+//   u_d:  along j from memory, along i through LDS, along k into the M^3
+//         points, where V_a += G_ad u_d (the thread's (jq, iq) line of points;
+//         the nine factors are streamed once);
+//   f:    J f and J' f along j; J, J' and J along i; J, J, J' along k give the
+//         three derivatives at the thread's points, c = sum_a V_a df/dr_a;
+//   out:  J^T along k from registers, along i through LDS, along j to memory.
+// V stays in registers and serves every field.
+//
+// FP64 vector and matrix products run at the same rate on gfx950, and the
+// matrix form of these stages used 12 of 16 rows in the interpolations and 8 of
+// 16 in the projections (and a branch per predicated access).  What bounds this
+// form is its stream with one field (the nine factors; 5.5 TB/s in FP64 at N =
+// 7) and its vector instructions with several.  Boxes of 4 million points, us
+// for one / four fields, matrix form -> this form:
+//   N      FP64                          FP32
+//   3      366/816 -> 226/311            243/521 -> 107/142
+//   5      293/614 -> 225/318            239/504 -> 111/151
+//   7      270/500 -> 212/322            160/295 -> 107/169
+//   9      354/694 -> 281/423            219/442 -> 116/173
+//   10     282/558 -> 194/304            252/510 -> 87/146
+// (Requesting a component's factors ahead into registers, as that form did,
+// costs occupancy here: 774 against 322 us.)
+template <int N, typename T>
+__global__ __launch_bounds__((AdvShape<N, T>::TPB))
+    __attribute__((amdgpu_waves_per_eu(N == 8 && sizeof(T) == 8 ? 3 : 1))) void adv_dealias_kernel(
+    int nf, const T* __restrict__ coef, const T* __restrict__ G, const T* __restrict__ u,
+    int64_t ustride, const T* __restrict__ f, T* __restrict__ out) {
+  typedef AdvShape<N, T> S;
+  typedef typename S::J J;
+  typedef typename S::JD JD;
+  typedef typename S::JT JT;
+  constexpr int n = S::n, M = S::M, P = S::P, Q = S::Q, n2 = S::n2, nM = S::nM, M2 = S::M2,
+                TPB = S::TPB, SA = S::SA, SY = S::SY, NY = S::NY;
+  __shared__ T sA[S::NA * S::A];
+  __shared__ T sY[NY * S::Y];
+  const T* cJ = coef;
+  const T* cJD = coef + J::SZ;
+  const T* cJT = cJD + JD::SZ;
+  const int t = threadIdx.x;
+  const int64_t eP = (int64_t)blockIdx.x * P;
+  const T* Ge = G + (int64_t)blockIdx.x * 9 * Q;
+  // this thread's node line along j (p = k n + i), its row of lines along i
+  // and its point line along k
+  const bool own_j = t < n2, own_k = t < M2;
+  const int jbase = (t / n) * n2 + t % n;             // node (k, 0, i)
+  const int abase = (t / n) * M * SA + t % n;         // sA place (k, jq = 0, i)
+  const int ybase = (t / M) * SY + t % M;             // sY place (k = 0, jq, iq)
+
+  // The line of the next field.  It is taken less the field's value at the
+  // element's first node: the derivatives do not see a constant, and the
+  // interpolations then round the field's variation over the element instead
+  // of its values.
+  T xf[n], f0;
+  auto fetch_f = [&](const T* __restrict__ fe) {
+    f0 = fe[0];
+#pragma unroll
+    for (int j = 0; j < n; ++j) xf[j] = own_j ? fe[jbase + j * n] : T(0);
   };
-  int64_t e = blockIdx.x;
-  if (e < E) fetch(e, 0);
-  for (; e < E; e += gridDim.x) {
-    const int64_t en = e + gridDim.x;
-    for (int q = threadIdx.x; q < 4 * P; q += kThreads) {
-      const int d = q / P, p = q - d * P;
-      sIn[q] = d < 3 ? u[d * ustride + e * P + p] : f[e * P + p];
-    }
-    __syncthreads();
+  fetch_f(f + eP);
 
-    // 1. V_a = sum_d G_ad (J x J x J) u_d, held in the last stage's tiles
-    V Va[TPW][3];
+  T V[3][M];
 #pragma unroll
-    for (int ti = 0; ti < TPW; ++ti)
+  for (int a = 0; a < 3; ++a)
 #pragma unroll
-      for (int a = 0; a < 3; ++a) Va[ti][a] = V{T(0), T(0), T(0), T(0)};
+    for (int q = 0; q < M; ++q) V[a][q] = T(0);
+  auto lines_j = [&](int d, int p, T* __restrict__ dst) {
+    const T* ud = u + d * ustride + eP + (p / n) * n2 + p % n;
+    T* w = dst + (p / n) * M * SA + p % n;
+    J([&](int j) { return ud[j * n]; }).apply(cJ, [&](int q, T y) { w[q * SA] = y; });
+  };
+  auto lines_i = [&](const T* __restrict__ src, T* __restrict__ dst, int r) {
+    J([&](int i) { return src[r * SA + i]; }).apply(cJ, [&](int q, T y) { dst[r * SY + q] = y; });
+  };
+  auto add_v = [&](int d, const T* __restrict__ src) {
+    const T* g = Ge + d * Q + t;
+    J([&](int k) { return src[ybase + k * M * SY]; }).apply(cJ, [&](int q, T y) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+        V[a][q] += __builtin_nontemporal_load(g + 3 * a * Q + q * M2) * y;
+    });
+  };
+  if constexpr (NY == 3) {
+    for (int p = t; p < 3 * n2; p += TPB) lines_j(p / n2, p % n2, sA + (p / n2) * S::A);
+    __syncthreads();
+    for (int r = t; r < 3 * nM; r += TPB)
+      lines_i(sA + (r / nM) * S::A, sY + (r / nM) * S::Y, r % nM);
+    __syncthreads();
+    if (own_k)
+#pragma unroll
+      for (int d = 0; d < 3; ++d) add_v(d, sY + d * S::Y);
+  } else {
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-      FOR_TILES(I0, I0::store(sX0, I0::tile(sIn + d * P, aJ, t, lane), t, lane));
+      if (own_j) lines_j(d, t, sA);
       __syncthreads();
-      FOR_TILES(I1, I1::store(sY, I1::tile(sX0, aJ, t, lane), t, lane));
+      if (t < nM) lines_i(sA, sY, t);
       __syncthreads();
-#pragma unroll
-      for (int ti = 0; ti < TPW; ++ti) {
-        const int t = wv + ti * kW;
-        if (t < I2::NT) {
-          const V ui = I2::tile(sY, aJ, t, lane);
-#pragma unroll
-          for (int a = 0; a < 3; ++a)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) Va[ti][a][r] += g[ti][a][r] * ui[r];
-        }
-      }
-      if (d < 2) fetch(e, d + 1);
-      else if (en < E) fetch(en, 0);
+      if (own_k) add_v(d, sY);
     }
+  }
 
-    // every field k advected by the same V
-    for (int k = 0; k < nf; ++k) {
-      if (k > 0) {
-        for (int q = threadIdx.x; q < P; q += kThreads)
-          sIn[3 * P + q] = f[k * ustride + e * P + q];
-        __syncthreads();
-      }
-      // 2. c = sum_a V_a df/dr_a: r (J x J x JD), s (J x JD x J), t (JD x J x J)
-      FOR_TILES(I0, I0::store(sX0, I0::tile(sIn + 3 * P, aJ, t, lane), t, lane);
-                I0::store(sX1, I0::tile(sIn + 3 * P, aJD, t, lane), t, lane));
-      __syncthreads();
-      V c[TPW];
+  for (int m = 0; m < nf; ++m) {
+    if (own_j) {
+      auto x = [&](int j) { return xf[j] - f0; };
+      J(x).apply(cJ, [&](int q, T y) { sA[abase + q * SA] = y; });
+      JD(x).apply(cJD, [&](int q, T y) { sA[S::A + abase + q * SA] = y; });
+    }
+    // the next field's line is on its way during this field
+    if (m + 1 < nf) fetch_f(f + (m + 1) * ustride + eP);
+    __syncthreads();
+    T c[M];
 #pragma unroll
-      for (int ti = 0; ti < TPW; ++ti) c[ti] = V{T(0), T(0), T(0), T(0)};
-      if constexpr (kMerge) {
-        FOR_TILES(I1, I1::store(sY, I1::tile(sX1, aJ, t, lane), t, lane);
-                  I1::store(sY + S::YS, I1::tile(sX0, aJD, t, lane), t, lane);
-                  I1::store(sY + 2 * S::YS, I1::tile(sX0, aJ, t, lane), t, lane));
-        __syncthreads();
-#pragma unroll
-        for (int ti = 0; ti < TPW; ++ti) {
-          const int t = wv + ti * kW;
-          if (t < I2::NT) {
-            // one derivative tile live at a time (the scheduler would
-            // otherwise hoist all of them and halve the occupancy)
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-              const V fa = I2::tile(sY + a * S::YS, a == 2 ? aJD : aJ, t, lane);
-#pragma unroll
-              for (int r = 0; r < 4; ++r) c[ti][r] += Va[ti][a][r] * fa[r];
-              __builtin_amdgcn_sched_barrier(0);
-            }
-          }
-        }
-        // (the c stores below touch sR only, whose arrays the phase above read
-        // before the barrier)
-      } else {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-          const T* src = a == 0 ? sX1 : sX0;
-          const T* a1 = a == 1 ? aJD : aJ;
-          const T* a2 = a == 2 ? aJD : aJ;
-          FOR_TILES(I1, I1::store(sY, I1::tile(src, a1, t, lane), t, lane));
-          __syncthreads();
-#pragma unroll
-          for (int ti = 0; ti < TPW; ++ti) {
-            const int t = wv + ti * kW;
-            if (t < I2::NT) {
-              const V fa = I2::tile(sY, a2, t, lane);
-#pragma unroll
-              for (int r = 0; r < 4; ++r) c[ti][r] += Va[ti][a][r] * fa[r];
-            }
-          }
-          __syncthreads();
+    for (int q = 0; q < M; ++q) c[q] = T(0);
+    // derivative a at this thread's points from its (jq, iq) lines
+    auto add_c = [&](auto dir, const T* __restrict__ src) {
+      constexpr int a = decltype(dir)::value;
+      auto x = [&](int k) { return src[ybase + k * M * SY]; };
+      auto put = [&](int q, T y) { c[q] += V[a][q] * y; };
+      if constexpr (a == 2) JD(x).apply(cJD, put);
+      else J(x).apply(cJ, put);
+    };
+    if constexpr (NY == 3) {
+      for (int r = t; r < 2 * nM; r += TPB) {
+        const int row = r % nM;
+        if (r < nM) {
+          auto x = [&](int i) { return sA[row * SA + i]; };
+          JD(x).apply(cJD, [&](int q, T y) { sY[row * SY + q] = y; });
+          J(x).apply(cJ, [&](int q, T y) { sY[2 * S::Y + row * SY + q] = y; });
+        } else {
+          lines_i(sA + S::A, sY + S::Y, row);
         }
       }
-      // c into the first region (its inputs and first-stage arrays are dead)
-      T* sC = sR;
-#pragma unroll
-      for (int ti = 0; ti < TPW; ++ti) {
-        const int t = wv + ti * kW;
-        if (t < I2::NT) I2::store(sC, c[ti], t, lane);
+      __syncthreads();
+      if (own_k) {
+        add_c(std::integral_constant<int, 0>(), sY);
+        add_c(std::integral_constant<int, 1>(), sY + S::Y);
+        add_c(std::integral_constant<int, 2>(), sY + 2 * S::Y);
+      }
+    } else {
+      if (t < nM) {
+        JD([&](int i) { return sA[t * SA + i]; }).apply(cJD, [&](int q, T y) { sY[t * SY + q] = y; });
       }
       __syncthreads();
-
-      // 3. out = (J^T x J^T x J^T) c
-      FOR_TILES(B2, B2::store(sY, B2::tile(sC, aJT, t, lane), t, lane));
+      if (own_k) add_c(std::integral_constant<int, 0>(), sY);
       __syncthreads();
-      FOR_TILES(B1, B1::store(sR, B1::tile(sY, aJT, t, lane), t, lane));
+      if (t < nM) lines_i(sA + S::A, sY, t);
       __syncthreads();
-      FOR_TILES(B0, B0::store(out + k * ustride + e * P, B0::tile(sR, aJT, t, lane), t, lane));
-      __syncthreads();  // sR is restaged next
+      if (own_k) add_c(std::integral_constant<int, 1>(), sY);
+      __syncthreads();
+      if (t < nM) lines_i(sA, sY, t);
+      __syncthreads();
+      if (own_k) add_c(std::integral_constant<int, 2>(), sY);
+    }
+    // project: along k (to the first region, whose lines are used up) ...
+    if (own_k) {
+      JT([&](int q) { return c[q]; })
+          .apply(cJT, [&](int k, T y) { sA[ybase + k * M * SY] = y; });
+    }
+    __syncthreads();
+    // ... along i ...
+    if (t < nM) {
+      JT([&](int q) { return sA[t * SY + q]; })
+          .apply(cJT, [&](int i, T y) { sY[t * SA + i] = y; });
+    }
+    __syncthreads();
+    // ... along j
+    if (own_j) {
+      T* w = out + m * ustride + eP + jbase;
+      JT([&](int q) { return sY[abase + q * SA]; })
+          .apply(cJT, [&](int j, T y) { w[j * n] = y; });
     }
   }
 }
@@ -433,7 +506,7 @@ __global__ void adv_metric_finish(int64_t E, int q1, const double* __restrict__ 
 }
 
 template <int N, typename T>
-hipError_t run_advect(const sem_mesh* m, int rule, int nf, const T* mats, const T* D, const T* G,
+hipError_t run_advect(const sem_mesh* m, int rule, int nf, const T* eo, const T* D, const T* G,
                       const T* u, const T* f, T* out, hipStream_t s) {
   const int64_t ustride = m->E * (int64_t)m->P;
   if (rule == 0) {
@@ -441,23 +514,8 @@ hipError_t run_advect(const sem_mesh* m, int rule, int nf, const T* mats, const 
                        nf, D, G, u, ustride, f, out);
     return hipGetLastError();
   }
-  // persistent grid: twice the resident workgroups (measured best of 1x, 2x)
-  static const int per_cu = [] {
-    int v = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, adv_dealias_kernel<N, T>,
-                                                     64 * adv_waves<N, T>(),
-                                                     0) != hipSuccess || v <= 0)
-      v = 1;
-    return v;
-  }();
-  int dev = 0, cus = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e != hipSuccess) return e;
-  int64_t grid = 2 * (int64_t)cus * per_cu;
-  if (grid > m->E) grid = m->E;
-  hipLaunchKernelGGL((adv_dealias_kernel<N, T>), dim3((unsigned)grid), dim3(64 * adv_waves<N, T>()), 0, s,
-                     m->E, nf, mats, G, u, ustride, f, out);
+  hipLaunchKernelGGL((adv_dealias_kernel<N, T>), dim3((unsigned)m->E),
+                     dim3(AdvShape<N, T>::TPB), 0, s, nf, eo, G, u, ustride, f, out);
   return hipGetLastError();
 }
 
@@ -504,20 +562,20 @@ hipError_t launch_adv_geometry(const sem_mesh* m, int q1, const double* mats, co
 }
 
 template <typename T>
-hipError_t launch_advect(const sem_mesh* m, int rule, int nf, const T* mats, const T* D,
+hipError_t launch_advect(const sem_mesh* m, int rule, int nf, const T* eo, const T* D,
                          const T* G, const T* u, const T* f, T* out, hipStream_t s) {
   if (nf <= 0) return hipSuccess;
   switch (m->N) {
-    case 1: return run_advect<1, T>(m, rule, nf, mats, D, G, u, f, out, s);
-    case 2: return run_advect<2, T>(m, rule, nf, mats, D, G, u, f, out, s);
-    case 3: return run_advect<3, T>(m, rule, nf, mats, D, G, u, f, out, s);
-    case 4: return run_advect<4, T>(m, rule, nf, mats, D, G, u, f, out, s);
-    case 5: return run_advect<5, T>(m, rule, nf, mats, D, G, u, f, out, s);
-    case 6: return run_advect<6, T>(m, rule, nf, mats, D, G, u, f, out, s);
-    case 7: return run_advect<7, T>(m, rule, nf, mats, D, G, u, f, out, s);
-    case 8: return run_advect<8, T>(m, rule, nf, mats, D, G, u, f, out, s);
-    case 9: return run_advect<9, T>(m, rule, nf, mats, D, G, u, f, out, s);
-    case 10: return run_advect<10, T>(m, rule, nf, mats, D, G, u, f, out, s);
+    case 1: return run_advect<1, T>(m, rule, nf, eo, D, G, u, f, out, s);
+    case 2: return run_advect<2, T>(m, rule, nf, eo, D, G, u, f, out, s);
+    case 3: return run_advect<3, T>(m, rule, nf, eo, D, G, u, f, out, s);
+    case 4: return run_advect<4, T>(m, rule, nf, eo, D, G, u, f, out, s);
+    case 5: return run_advect<5, T>(m, rule, nf, eo, D, G, u, f, out, s);
+    case 6: return run_advect<6, T>(m, rule, nf, eo, D, G, u, f, out, s);
+    case 7: return run_advect<7, T>(m, rule, nf, eo, D, G, u, f, out, s);
+    case 8: return run_advect<8, T>(m, rule, nf, eo, D, G, u, f, out, s);
+    case 9: return run_advect<9, T>(m, rule, nf, eo, D, G, u, f, out, s);
+    case 10: return run_advect<10, T>(m, rule, nf, eo, D, G, u, f, out, s);
     default: return hipErrorInvalidValue;
   }
 }
