@@ -749,8 +749,11 @@ sem_status sem_setup_mesh(const sem_mesh_desc* desc, void* stream, sem_mesh** ou
   SEM_HIP(hipGetDevice(&m->device));
 
   const int n1 = N + 1;
-  std::vector<double> Dh(n1 * n1 + n1);
-  if ((st = host_gll(N, nullptr, Dh.data() + n1 * n1, Dh.data()))) return st;
+  // D, the weights, the nodes, the weights again (nodes and weights adjoin)
+  std::vector<double> Dh(n1 * n1 + 3 * n1);
+  double* tail = Dh.data() + n1 * n1;
+  if ((st = host_gll(N, tail + n1, tail, Dh.data()))) return st;
+  std::memcpy(tail + 2 * n1, tail, n1 * sizeof(double));
   std::memcpy(m->h_D, Dh.data(), n1 * n1 * sizeof(double));
   std::vector<float> D32(n1 * n1);
   for (int a = 0; a < n1 * n1; ++a) D32[a] = (float)Dh[a];
@@ -763,16 +766,23 @@ sem_status sem_setup_mesh(const sem_mesh_desc* desc, void* stream, sem_mesh** ou
     return st;
   {
     DevBuf dxyz, dbad;
-    if ((st = dxyz.ensure((size_t)3 * nL * sizeof(double))) || (st = dbad.ensure(sizeof(int))))
+    if ((st = dxyz.ensure((size_t)3 * nL * sizeof(double))) ||
+        (st = dbad.ensure(2 * sizeof(int))) ||
+        (st = m->geo.ensure((size_t)E * 21 * sizeof(double))))
       return st;
     SEM_HIP(hipMemcpyAsync(dxyz.p, desc->xyz, (size_t)3 * nL * sizeof(double),
                            hipMemcpyHostToDevice, s));
-    SEM_HIP(launch_fill<int>(dbad.as<int>(), 1, 0, s));
+    SEM_HIP(launch_fill<int>(dbad.as<int>(), 2, 0, s));
     SEM_HIP(launch_geometry(m.get(), dxyz.as<double>(), m->G64.as<double>(), m->B64.as<double>(),
                             m->G32.as<float>(), m->B32.as<float>(), dbad.as<int>(), s));
-    int bad = 0;
-    SEM_HIP(hipMemcpyAsync(&bad, dbad.p, sizeof(int), hipMemcpyDeviceToHost, s));
+    SEM_HIP(launch_straight(m.get(), dxyz.as<double>(), m->geo.as<double>(), dbad.as<int>() + 1,
+                            s));
+    int flags[2] = {0, 0};
+    SEM_HIP(hipMemcpyAsync(flags, dbad.p, sizeof(flags), hipMemcpyDeviceToHost, s));
     SEM_HIP(hipStreamSynchronize(s));
+    const int bad = flags[0];
+    m->straight = flags[1] == 0;
+    if (!m->straight) m->geo.release();
     if (bad > 0)
       return fail(SEM_EINVAL, "element map is not orientation-preserving (detJ <= 0) at " +
                                   std::to_string(bad) + " points");
@@ -1318,6 +1328,11 @@ sem_status sem_ax_backward(const sem_mesh* m, const double* u, const double* wba
   if (!(h2 >= 0.0) || !std::isfinite(h2)) return fail(SEM_EINVAL, "h2 must be finite and >= 0");
   if (ubar == wbar) return fail(SEM_EINVAL, "ubar must not alias wbar");
   hipStream_t s = (hipStream_t)stream;
+  if (ubar && kbar && ubar != u) {  // ubar in place of u: kbar then reads ubar
+    hipError_t e = launch_ax_backward(m, u, wbar, k, h2, ubar, kbar, s);
+    if (e != hipSuccess) return hip_fail(e, "sem_ax_backward");
+    return SEM_OK;
+  }
   if (ubar) {
     hipError_t e = launch_ax<double>(m, wbar, nullptr, ubar, k, h2, m->G64.as<double>(),
                                      m->B64.as<double>(), m->D64.as<double>(), s);

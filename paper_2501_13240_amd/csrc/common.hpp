@@ -234,6 +234,10 @@ struct sem_mesh {
   double h_D[(sem::kMaxOrder + 1) * (sem::kMaxOrder + 1)];
   sem::DevBuf D64, D32;                 // derivative matrix
   sem::DevBuf G64, B64, G32, B32;       // geometry [E][6][P], [E][P]
+  // every element is the trilinear image of its corners up to rounding; geo
+  // [E][21]: its coefficients (see launch_straight)
+  bool straight = false;
+  sem::DevBuf geo;
   sem::DevBuf lmap, fseg, fperm;        // solver numbering (free unique nodes)
   sem::DevBuf lmap2;                    // in-solve operator routing (see launch_ax_split)
   sem::DevBuf fperm2;                   // fperm with shared copies at their surface slots
@@ -292,12 +296,22 @@ int ax_split_parts(int N, bool f64);
 // kbar = sign sum_ab (D_a wbar) G_ab (D_b u) at every local point
 hipError_t launch_ax_kbar(const sem_mesh* m, const double* u, const double* wbar, double* kbar,
                           double sign, hipStream_t s);
+// ubar = A_L(k) wbar and kbar (sign +1) together
+hipError_t launch_ax_backward(const sem_mesh* m, const double* u, const double* wbar,
+                              const double* k, double h2, double* ubar, double* kbar,
+                              hipStream_t s);
 template <typename T>
 hipError_t launch_mass(int64_t n, const T* B, const T* u, T* w, hipStream_t s);
 
 // setup
 hipError_t launch_geometry(const sem_mesh* m, const double* xyz, double* G, double* B, float* G32,
                            float* B32, int* bad_count, hipStream_t s);
+// geo [E][21] <- the coefficient vectors x_r, x_s, x_t, x_rs, x_rt, x_st, x_rst
+// of each element's trilinear map through its corners; *curved (zeroed by the
+// caller) counts elements with a node off that map by more than the rounding
+// of coordinates of its size
+hipError_t launch_straight(const sem_mesh* m, const double* xyz, double* geo, int* curved,
+                           hipStream_t s);
 hipError_t launch_local_diag(const sem_mesh* m, const double* k, double h2, double* dL,
                              hipStream_t s);
 

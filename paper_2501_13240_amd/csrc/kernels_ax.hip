@@ -301,7 +301,8 @@ struct MShape {
 constexpr int ax_waves(int N, int bytes) {
   return N == 5 ? 1 : N == 6 ? (bytes == 8 ? 2 : 3) : N == 10 ? 8 : 4;
 }
-constexpr int ax_min_waves(int N, int bytes) {
+constexpr int ax_min_waves(int N, int bytes, int geo) {
+  if (geo) return N == 7 ? 5 : N == 5 || N == 9 ? 3 : 4;
   return bytes == 8 ? (N == 5 || N == 9 ? 3 : N == 7 ? 6 : 4)
                     : (N == 5 || N == 9 ? 5 : N == 6 || N == 7 ? 8 : 7);
 }
@@ -330,25 +331,56 @@ __device__ __forceinline__ int lds_point(int q) {
   return S::LS == S::n1 ? q : (q / S::n1) * S::LS + q % S::n1;
 }
 
-// Fragments of D (forward) and D^T: the row of a product's result register r
-// in lane group kk is kk + 4 r in both precisions (FP32 results come in rows
-// 4 kk + r, so the rows of its operand are taken in that order; every lane
-// then has KS result rows), and step s contracts the columns kk + 4 s.
-template <int N, typename T>
-__device__ __forceinline__ void d_frags(const T* __restrict__ D, int lane,
-                                        T (&af)[LShape<N, T>::KS], T (&at)[LShape<N, T>::KS]) {
-  constexpr int n1 = N + 1;
-  const int i = lane & 15, kk = lane >> 4;
-  const int row = sizeof(T) == 8 ? i : (i >> 2) + 4 * (i & 3), rc = min(row, n1 - 1);
+// Fragments of D (forward) and D^T.  In both precisions the row of result r in
+// lane group kk is kk + 4 r, and step s contracts the columns kk + 4 s, so
+// every lane has KS result rows (FP32 results of 16x16x4 products come in rows
+// 4 kk + r, so the rows of the operand are taken in that order).
+// BLK (FP64): products of four 4x4x4 blocks, whose blocks are the four column
+// groups of a tile (A[i][k] of every block in lane i + 4 b + 16 k, B[k][j] and
+// the result's row k, column 4 b + j in lane 16 k + 4 b + j): KS x KS of them
+// cover 4 KS rows, where the 16x16x4 form always computes 16 (N = 7: 8 used) at
+// the same rate.  The straight-edged operator, which computes more than it
+// streams, gains by them (8 million points, N = 7: 73 -> 64 us); the streaming
+// one loses by their larger number (82 -> 87 us).
+template <int N, typename T, bool BLK>
+struct DFrag {
+  static_assert(!BLK || sizeof(T) == 8, "4x4x4 blocks are FP64");
+  static constexpr int n1 = N + 1, KS = LShape<N, T>::KS, R = BLK ? KS : 1;
+  T m[R][KS];
+  DFrag() = default;
+  __device__ __forceinline__ DFrag(const T* __restrict__ D, int lane, bool trans) {
+    const int i = lane & 15, kk = lane >> 4;
 #pragma unroll
-  for (int s = 0; s < LShape<N, T>::KS; ++s) {
-    const int l = 4 * s + kk, lc = min(l, n1 - 1);
-    const T f = D[rc * n1 + lc], t = D[lc * n1 + rc];
-    const bool ok = row < n1 && l < n1;
-    af[s] = ok ? f : T(0);
-    at[s] = ok ? t : T(0);
+    for (int r = 0; r < R; ++r) {
+      const int row = BLK ? 4 * r + (i & 3) : sizeof(T) == 8 ? i : (i >> 2) + 4 * (i & 3);
+      const int rc = min(row, n1 - 1);
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        const int l = 4 * s + kk, lc = min(l, n1 - 1);
+        const T v = trans ? D[lc * n1 + rc] : D[rc * n1 + lc];
+        m[r][s] = row < n1 && l < n1 ? v : T(0);
+      }
+    }
   }
-}
+  // out[r] = rows kk + 4 r of the matrix times the tile with operands x[s]
+  __device__ __forceinline__ void mul(const T (&x)[KS], T (&out)[KS]) const {
+    if constexpr (BLK) {
+#pragma unroll
+      for (int r = 0; r < KS; ++r) out[r] = 0.0;
+#pragma unroll
+      for (int s = 0; s < KS; ++s)
+#pragma unroll
+        for (int r = 0; r < KS; ++r)
+          out[r] = __builtin_amdgcn_mfma_f64_4x4x4f64(m[r][s], x[s], out[r], 0, 0, 0);
+    } else {
+      typename Mm<T>::V acc = {T(0), T(0), T(0), T(0)};
+#pragma unroll
+      for (int s = 0; s < KS; ++s) acc = Mm<T>::mma(m[0][s], x[s], acc);
+#pragma unroll
+      for (int r = 0; r < KS; ++r) out[r] = acc[r];
+    }
+  }
+};
 
 // The three contractions of one 16-column tile: along i from si, along j
 // from sj, along k from sk (element blocks in LDS), results to ri, rj, rk at
@@ -356,8 +388,8 @@ __device__ __forceinline__ void d_frags(const T* __restrict__ D, int lane,
 // predicated: columns past the last one repeat it (the same values to the same
 // places) and contraction indices past n1 repeat the last one against zero
 // fragments.
-template <int N, typename T>
-__device__ __forceinline__ void contract_tile(int tile, int lane, const T (&m)[LShape<N, T>::KS],
+template <int N, typename T, bool BLK>
+__device__ __forceinline__ void contract_tile(int tile, int lane, const DFrag<N, T, BLK>& m,
                                               const T* si, const T* sj, const T* sk, T* ri,
                                               T* rj, T* rk) {
   using S = LShape<N, T>;
@@ -366,7 +398,7 @@ __device__ __forceinline__ void contract_tile(int tile, int lane, const T (&m)[L
   const int col = min(tile * 16 + (lane & 15), S::P2 - 1);
   const int cq = col / n1, cr = col % n1;
   const int bi = cq * PS + cr * LS, bj = cq * PS + cr, bk = cq * LS + cr;
-  T xi[KS], xj[KS], xk[KS];
+  T xi[KS], xj[KS], xk[KS], ai[KS], aj[KS], ak[KS];
 #pragma unroll
   for (int s = 0; s < KS; ++s) {
     const int l = 4 * s + 3 < n1 ? kk + 4 * s : min(kk + 4 * s, n1 - 1);
@@ -374,13 +406,9 @@ __device__ __forceinline__ void contract_tile(int tile, int lane, const T (&m)[L
     xj[s] = sj[bj + l * LS];
     xk[s] = sk[bk + l * PS];
   }
-  typename Mm<T>::V ai = {T(0), T(0), T(0), T(0)}, aj = ai, ak = ai;
-#pragma unroll
-  for (int s = 0; s < KS; ++s) {
-    ai = Mm<T>::mma(m[s], xi[s], ai);
-    aj = Mm<T>::mma(m[s], xj[s], aj);
-    ak = Mm<T>::mma(m[s], xk[s], ak);
-  }
+  m.mul(xi, ai);
+  m.mul(xj, aj);
+  m.mul(xk, ak);
 #pragma unroll
   for (int r = 0; r < KS; ++r) {
     const int row = kk + 4 * r;
@@ -390,6 +418,47 @@ __device__ __forceinline__ void contract_tile(int tile, int lane, const T (&m)[L
       rk[bk + row * PS] = ak[r];
     }
   }
+}
+
+// Metric of a straight-edged element (the trilinear image of its corners) at
+// the point (r, s, t) with quadrature weight wq, from the element's seven
+// coefficient vectors c = (x_r, x_s, x_t, x_rs, x_rt, x_st, x_rst): g =
+// (rr, rs, rt, ss, st, tt) as stored factors hold them, and B.  In FP64 also
+// where the operator runs in FP32, so that its factors round as the stored ones.
+typedef const double __attribute__((address_space(4))) * UniformD;  // read by scalar loads
+__device__ __forceinline__ void straight_metric(UniformD c, double r, double s, double t,
+                                                double wq, double (&g)[6], double& B) {
+  double xr[3], xs[3], xt[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const double rs = c[9 + d], rt = c[12 + d], st = c[15 + d], rst = c[18 + d];
+    const double a = st + rst * r;
+    xr[d] = (c[d] + rs * s) + (rt + rst * s) * t;
+    xs[d] = (c[3 + d] + rs * r) + a * t;
+    xt[d] = (c[6 + d] + rt * r) + a * s;
+  }
+  double A[3][3];  // detJ grad r, grad s, grad t
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const int e = (d + 1) % 3, f = (d + 2) % 3;
+    A[0][d] = xs[e] * xt[f] - xs[f] * xt[e];
+    A[1][d] = xt[e] * xr[f] - xt[f] * xr[e];
+    A[2][d] = xr[e] * xs[f] - xr[f] * xs[e];
+  }
+  const double det = xr[0] * A[0][0] + xr[1] * A[0][1] + xr[2] * A[0][2];
+  // 1 / det by two Newton steps on the hardware's estimate (a full division
+  // also handles what a determinant checked positive cannot be)
+  double rd = __builtin_amdgcn_rcp(det);
+  rd = rd * (2.0 - det * rd);
+  rd = rd * (2.0 - det * rd);
+  const double sc = wq * rd;
+  B = wq * det;
+  g[0] = sc * (A[0][0] * A[0][0] + A[0][1] * A[0][1] + A[0][2] * A[0][2]);
+  g[1] = sc * (A[0][0] * A[1][0] + A[0][1] * A[1][1] + A[0][2] * A[1][2]);
+  g[2] = sc * (A[0][0] * A[2][0] + A[0][1] * A[2][1] + A[0][2] * A[2][2]);
+  g[3] = sc * (A[1][0] * A[1][0] + A[1][1] * A[1][1] + A[1][2] * A[1][2]);
+  g[4] = sc * (A[1][0] * A[2][0] + A[1][1] * A[2][1] + A[1][2] * A[2][2]);
+  g[5] = sc * (A[2][0] * A[2][0] + A[2][1] * A[2][1] + A[2][2] * A[2][2]);
 }
 
 // Operator with matrix-core contractions in T, one element per workgroup:
@@ -418,12 +487,22 @@ __device__ __forceinline__ void contract_tile(int tile, int lane, const T (&m)[L
 // larger than the memory-side cache).  MODE 4 / 5: MODE 2 / 3 without the
 // wavefront sums (a Chebyshev pass needs none).  MODE 6 / 7: MODE 2 / 3 with
 // p w only (sum(w) serves the null-space projection alone).
-template <int N, typename T, int MODE>
+//
+// GEO 0: factors from G and B.  GEO 1 (every element of the mesh is straight-
+// edged; FP64 only): formed per point from the element's coefficients (geo, 21
+// per element; pts: the GLL nodes and weights): 16 B per point.  In FP32 the
+// same arithmetic costs more than the 24 B it saves (N = 7: 53 against 43 us).
+// FP64 with k and h2 on 8 million points, stored -> straight-edged, us:
+//   N = 5 106 -> 88, 6 118 -> 85, 7 99 -> 74, 8 108 -> 88, 9 107 -> 84, 10 112 -> 92;
+// bound by its FP64 operations (about 150 per point, products and vector
+// instructions in the same units) and LDS passes.
+template <int N, typename T, int MODE, int GEO>
 __global__ __launch_bounds__((LShape<N, T>::TPB))
-    __attribute__((amdgpu_waves_per_eu(ax_min_waves(N, sizeof(T))))) void ax_line_kernel(
+    __attribute__((amdgpu_waves_per_eu(ax_min_waves(N, sizeof(T), GEO)))) void ax_line_kernel(
         const T* __restrict__ u, const int32_t* __restrict__ lmap, T* __restrict__ w,
         const T* __restrict__ kf, const T h2, const T* __restrict__ G, const T* __restrict__ B,
-        const T* __restrict__ D, const int32_t* __restrict__ skip, T* __restrict__ wf,
+        const T* __restrict__ D, const double* __restrict__ geo,
+        const double* __restrict__ pts, const int32_t* __restrict__ skip, T* __restrict__ wf,
         double* __restrict__ epart) {
   using S = LShape<N, T>;
   constexpr int n1 = S::n1, P = S::P, KS = S::KS, PPT = S::PPT, TPB = S::TPB, NW = S::NW,
@@ -459,13 +538,20 @@ __global__ __launch_bounds__((LShape<N, T>::TPB))
   for (int s = 0; s < PPT; ++s) {
     const uint32_t q = point(s);
     if constexpr (MODE == 0) uq[s] = ld_stream(u + eP + q);
-#pragma unroll
-    for (int c = 0; c < 6; ++c) gq[s][c] = ld_stream(Ge + c * P + q);
     kq[s] = use_k ? ld_stream(kf + eP + q) : T(1);
-    bq[s] = use_h2 ? ld_stream(B + eP + q) : T(0);
+    if constexpr (GEO == 0) {
+#pragma unroll
+      for (int c = 0; c < 6; ++c) gq[s][c] = ld_stream(Ge + c * P + q);
+      bq[s] = use_h2 ? ld_stream(B + eP + q) : T(0);
+    }
   }
-  T af[KS], at[KS];
-  d_frags<N, T>(D, lane, af, at);
+  // the straight-edged form's D^T is fetched behind the forward contractions
+  const DFrag<N, T, GEO == 1> af(D, lane, false);
+  DFrag<N, T, GEO == 1> at;
+  if constexpr (GEO == 0) at = DFrag<N, T, GEO == 1>(D, lane, true);
+  __shared__ double sp[GEO == 1 ? 2 * n1 : 1];  // nodes and weights
+  if constexpr (GEO == 1)
+    if (t < 2 * n1) sp[t] = pts[t];
   if constexpr (MODE >= 1) {
 #pragma unroll
     for (int s = 0; s < PPT; ++s) {
@@ -482,13 +568,19 @@ __global__ __launch_bounds__((LShape<N, T>::TPB))
   for (int x = 0; x < TPW; ++x) {
     const int tile = wv + x * NW;
     if ((x + 1) * NW <= NT || tile < NT)
-      contract_tile<N, T>(tile, lane, af, su, su, su, sa[0], sa[1], sa[2]);
+      contract_tile<N, T, GEO == 1>(tile, lane, af, su, su, su, sa[0], sa[1], sa[2]);
   }
+  if constexpr (GEO == 1) at = DFrag<N, T, true>(D, lane, true);
   __syncthreads();
   // metric and k
 #pragma unroll
   for (int s = 0; s < PPT; ++s) {
     const int q = lds_point<N, T>(point(s));
+    if constexpr (GEO == 1) {
+      const int p = (int)point(s), i = p % n1, j = (p / n1) % n1, k = p / (n1 * n1);
+      straight_metric((UniformD)(uintptr_t)(geo + e * 21), sp[i], sp[j], sp[k],
+                      sp[n1 + i] * sp[n1 + j] * sp[n1 + k], gq[s], bq[s]);
+    }
     const T ur = sa[0][q], us = sa[1][q], ut = sa[2][q];
     const T* gc = gq[s];
     T vr = gc[0] * ur + gc[1] * us + gc[2] * ut;
@@ -504,13 +596,15 @@ __global__ __launch_bounds__((LShape<N, T>::TPB))
       sa[1][q] = vs;
       sa[2][q] = vt;
     }
+    // the straight-edged form's factors live for one point
+    if constexpr (GEO == 1) __builtin_amdgcn_sched_barrier(0);
   }
   __syncthreads();
 #pragma unroll
   for (int x = 0; x < TPW; ++x) {
     const int tile = wv + x * NW;
     if ((x + 1) * NW <= NT || tile < NT)
-      contract_tile<N, T>(tile, lane, at, sa[0], sa[1], sa[2], sa[0], sa[1], sa[2]);
+      contract_tile<N, T, GEO == 1>(tile, lane, at, sa[0], sa[1], sa[2], sa[0], sa[1], sa[2]);
   }
   __syncthreads();
   double ps[2] = {0.0, 0.0};
@@ -736,6 +830,123 @@ bool prefer_mfma(int N, bool gather, bool fp32) {
   return N >= 5;
 }
 
+// Both gradients of w = A_L(k) u for a cotangent wbar in one pass, one element
+// per workgroup (the phases of ax_line_kernel with u carried through the
+// forward contractions as well): ubar = A_L(k) wbar and kbar = sum_ab (D_a wbar)
+// G_ab (D_b u).  One read of the factors serves both (88 B per point instead
+// of 152 with k and h2; 40 B on straight-edged elements): 8 million points, N =
+// 7, 190 -> 110 us (straight-edged 84 us).
+template <int N, int GEO>
+__global__ __launch_bounds__((LShape<N, double>::TPB))
+    __attribute__((amdgpu_waves_per_eu(N == 7 ? 5 : N == 10 ? 4 : 3))) void ax_backward_kernel(
+    const double* __restrict__ u, const double* __restrict__ wbar, const double* __restrict__ kf,
+    const double h2, const double* __restrict__ G, const double* __restrict__ B,
+    const double* __restrict__ D, const double* __restrict__ geo, const double* __restrict__ pts,
+    double* __restrict__ ubar, double* __restrict__ kbar) {
+  typedef double T;
+  using S = LShape<N, T>;
+  constexpr int n1 = S::n1, P = S::P, KS = S::KS, PPT = S::PPT, TPB = S::TPB, NW = S::NW,
+                NT = S::NT, TPW = S::TPW, SZ = n1 * S::PS;
+  __shared__ T su[SZ];
+  __shared__ T sa[3][SZ];
+  const int t = threadIdx.x, lane = t & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int64_t e = blockIdx.x;
+  const bool use_k = kf != nullptr;
+  const bool use_h2 = h2 != 0.0;
+  const T* Ge = G + e * 6 * P;
+  const int64_t eP = e * P;
+  auto point = [&](int s) -> uint32_t {
+    return (s + 1) * TPB <= P ? t + s * TPB : min(t + s * TPB, P - 1);
+  };
+  auto in_element = [&](int s) { return (s + 1) * TPB <= P || t + s * TPB < P; };
+  T wq[PPT], uq[PPT], gq[PPT][6], kq[PPT], bq[PPT];
+#pragma unroll
+  for (int s = 0; s < PPT; ++s) {
+    const uint32_t q = point(s);
+    wq[s] = ld_stream(wbar + eP + q);
+    uq[s] = ld_stream(u + eP + q);
+    kq[s] = use_k ? ld_stream(kf + eP + q) : T(1);
+    if constexpr (GEO == 0) {
+#pragma unroll
+      for (int c = 0; c < 6; ++c) gq[s][c] = ld_stream(Ge + c * P + q);
+      bq[s] = use_h2 ? ld_stream(B + eP + q) : T(0);
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < PPT; ++s) su[lds_point<N, T>(point(s))] = uq[s];
+  const DFrag<N, T, GEO == 1> af(D, lane, false);
+  __shared__ double sp[GEO == 1 ? 2 * n1 : 1];
+  if constexpr (GEO == 1)
+    if (t < 2 * n1) sp[t] = pts[t];
+  __syncthreads();
+  auto forward = [&](const T* src) {
+#pragma unroll
+    for (int x = 0; x < TPW; ++x) {
+      const int tile = wv + x * NW;
+      if ((x + 1) * NW <= NT || tile < NT)
+        contract_tile<N, T, GEO == 1>(tile, lane, af, src, src, src, sa[0], sa[1], sa[2]);
+    }
+    __syncthreads();
+  };
+  // the gradient of u at this lane's points first, then that of wbar
+  T ud[PPT][3];
+  forward(su);
+#pragma unroll
+  for (int s = 0; s < PPT; ++s) {
+    const int q = lds_point<N, T>(point(s));
+#pragma unroll
+    for (int d = 0; d < 3; ++d) ud[s][d] = sa[d][q];
+    su[q] = wq[s];
+  }
+  __syncthreads();
+  forward(su);
+  const DFrag<N, T, GEO == 1> at(D, lane, true);
+#pragma unroll
+  for (int s = 0; s < PPT; ++s) {
+    const int q = lds_point<N, T>(point(s));
+    if constexpr (GEO == 1) {
+      const int p = (int)point(s), i = p % n1, j = (p / n1) % n1, k = p / (n1 * n1);
+      straight_metric((UniformD)(uintptr_t)(geo + e * 21), sp[i], sp[j], sp[k],
+                      sp[n1 + i] * sp[n1 + j] * sp[n1 + k], gq[s], bq[s]);
+    }
+    const T wr = sa[0][q], ws = sa[1][q], wt = sa[2][q];
+    const T* gc = gq[s];
+    T vr = gc[0] * wr + gc[1] * ws + gc[2] * wt;
+    T vs = gc[1] * wr + gc[3] * ws + gc[4] * wt;
+    T vt = gc[2] * wr + gc[4] * ws + gc[5] * wt;
+    const T kb = ud[s][0] * vr + ud[s][1] * vs + ud[s][2] * vt;
+    if (use_k) {
+      vr *= kq[s];
+      vs *= kq[s];
+      vt *= kq[s];
+    }
+    if (in_element(s)) {
+      st_stream(kb, kbar + eP + point(s));
+      sa[0][q] = vr;
+      sa[1][q] = vs;
+      sa[2][q] = vt;
+    }
+    if constexpr (GEO == 1) __builtin_amdgcn_sched_barrier(0);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int x = 0; x < TPW; ++x) {
+    const int tile = wv + x * NW;
+    if ((x + 1) * NW <= NT || tile < NT)
+      contract_tile<N, T, GEO == 1>(tile, lane, at, sa[0], sa[1], sa[2], sa[0], sa[1], sa[2]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int s = 0; s < PPT; ++s) {
+    const uint32_t q = point(s);
+    const int ql = lds_point<N, T>(q);
+    T acc = (sa[0][ql] + sa[1][ql]) + sa[2][ql];
+    if (use_h2) acc += h2 * bq[s] * wq[s];
+    if (in_element(s)) st_stream(acc, ubar + eP + q);
+  }
+}
+
 // kbar_q = sign sum_ab (D_a wbar)_q G_ab,q (D_b u)_q: the derivative of the
 // operator in k contracted with a cotangent (same mapping, 72 B per point);
 // sign = -1 gives the gradient of a solve (exact negation).
@@ -831,17 +1042,31 @@ hipError_t run_ax_mfma16(const sem_mesh* m, const float* u, const int32_t* lmap,
   return hipGetLastError();
 }
 
+// the nodes and weights behind D in the FP64 buffer (see sem_setup_mesh)
+inline const double* gll_points(const sem_mesh* m) {
+  return m->D64.as<double>() + m->n1 * m->n1 + m->n1;
+}
+
+#define SEM_AX_LINE(MD, lm, wfree, ep)                                                          \
+  do {                                                                                         \
+    constexpr int kGeo = sizeof(T) == 8 ? 1 : 0;                                               \
+    if (kGeo && m->straight)                                                                   \
+      SEM_LAUNCH(ev0, ev1, (ax_line_kernel<N, T, MD, kGeo>), grid, block, s, u, lm, w, k, h2, G, \
+                 B, D, m->geo.as<double>(), gll_points(m), skip, wfree, ep);                   \
+    else                                                                                       \
+      SEM_LAUNCH(ev0, ev1, (ax_line_kernel<N, T, MD, 0>), grid, block, s, u, lm, w, k, h2, G, B, \
+                 D, (const double*)nullptr, (const double*)nullptr, skip, wfree, ep);          \
+  } while (0)
+
 template <int N, typename T>
 hipError_t run_ax_line(const sem_mesh* m, const T* u, const int32_t* lmap, T* w, const T* k, T h2,
                        const T* G, const T* B, const T* D, hipStream_t s, const int32_t* skip,
                        hipEvent_t ev0, hipEvent_t ev1) {
   const dim3 grid((unsigned)m->E), block(LShape<N, T>::TPB);
   if (lmap)
-    SEM_LAUNCH(ev0, ev1, (ax_line_kernel<N, T, 1>), grid, block, s, u, lmap, w, k, h2, G, B, D,
-               skip, (T*)nullptr, (double*)nullptr);
+    SEM_AX_LINE(1, lmap, (T*)nullptr, (double*)nullptr);
   else
-    SEM_LAUNCH(ev0, ev1, (ax_line_kernel<N, T, 0>), grid, block, s, u, lmap, w, k, h2, G, B, D,
-               skip, (T*)nullptr, (double*)nullptr);
+    SEM_AX_LINE(0, lmap, (T*)nullptr, (double*)nullptr);
   return hipGetLastError();
 }
 
@@ -912,7 +1137,7 @@ template hipError_t launch_ax<float>(const sem_mesh*, const float*, const int32_
 
 namespace {
 template <int N, typename T>
-hipError_t run_ax_split(const sem_mesh* m, const T* u, T* wf, T* wL, double* epart, bool mean_sums,
+hipError_t run_ax_split(const sem_mesh* m, const T* u, T* wf, T* w, double* epart, bool mean_sums,
                         const T* k, T h2, const T* G, const T* B, const T* D, hipStream_t s,
                         const int32_t* skip, hipEvent_t ev0, hipEvent_t ev1) {
   if constexpr (has_mfma(N)) {
@@ -928,10 +1153,9 @@ hipError_t run_ax_split(const sem_mesh* m, const T* u, T* wf, T* wL, double* epa
     const int mode = !epart ? (plain ? 4 : 5) : mean_sums ? (plain ? 2 : 3) : (plain ? 6 : 7);
     const dim3 grid((unsigned)m->E), block(LShape<N, T>::TPB);
     const int32_t* lm = m->lmap2.as<int32_t>();
-#define SEM_SPLIT_CASE(MD)                                                                   \
-  case MD:                                                                                   \
-    SEM_LAUNCH(ev0, ev1, (ax_line_kernel<N, T, MD>), grid, block, s, u, lm, wL, k, h2, G, B, D,  \
-               skip, wf, epart);                                                    \
+#define SEM_SPLIT_CASE(MD) \
+  case MD:                 \
+    SEM_AX_LINE(MD, lm, wf, epart); \
     break;
     switch (mode) {
       SEM_SPLIT_CASE(2)
@@ -1007,6 +1231,43 @@ hipError_t launch_ax_kbar(const sem_mesh* m, const double* u, const double* wbar
     case 10: return run_kbar<10>(m, u, wbar, kbar, sign, s);
     default: return hipErrorInvalidValue;
   }
+}
+
+namespace {
+template <int N>
+hipError_t run_backward(const sem_mesh* m, const double* u, const double* wbar, const double* k,
+                        double h2, double* ubar, double* kbar, hipStream_t s) {
+  const dim3 grid((unsigned)m->E), block(LShape<N, double>::TPB);
+  const double *G = m->G64.as<double>(), *B = m->B64.as<double>(), *D = m->D64.as<double>();
+  if (m->straight)
+    hipLaunchKernelGGL((ax_backward_kernel<N, 1>), grid, block, 0, s, u, wbar, k, h2, G, B, D,
+                       m->geo.as<double>(), gll_points(m), ubar, kbar);
+  else
+    hipLaunchKernelGGL((ax_backward_kernel<N, 0>), grid, block, 0, s, u, wbar, k, h2, G, B, D,
+                       (const double*)nullptr, (const double*)nullptr, ubar, kbar);
+  return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_ax_backward(const sem_mesh* m, const double* u, const double* wbar,
+                              const double* k, double h2, double* ubar, double* kbar,
+                              hipStream_t s) {
+  // the matrix-core form writes ubar and kbar element by element after reading
+  // u and wbar there; forced scalar operators (and N < 5) run the two apart
+  if (has_mfma(m->N) && ax_choice() != AxChoice::Scalar) {
+    switch (m->N) {
+      case 5: return run_backward<5>(m, u, wbar, k, h2, ubar, kbar, s);
+      case 6: return run_backward<6>(m, u, wbar, k, h2, ubar, kbar, s);
+      case 7: return run_backward<7>(m, u, wbar, k, h2, ubar, kbar, s);
+      case 8: return run_backward<8>(m, u, wbar, k, h2, ubar, kbar, s);
+      case 9: return run_backward<9>(m, u, wbar, k, h2, ubar, kbar, s);
+      case 10: return run_backward<10>(m, u, wbar, k, h2, ubar, kbar, s);
+      default: break;
+    }
+  }
+  const hipError_t e = launch_ax<double>(m, wbar, nullptr, ubar, k, h2, m->G64.as<double>(),
+                                         m->B64.as<double>(), m->D64.as<double>(), s);
+  return e != hipSuccess ? e : launch_ax_kbar(m, u, wbar, kbar, 1.0, s);
 }
 
 template <typename T>

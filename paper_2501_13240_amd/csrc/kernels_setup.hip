@@ -102,7 +102,68 @@ __global__ void local_diag_kernel(const double* __restrict__ G, const double* __
   }
 }
 
+// One workgroup per element: its trilinear map x = sum_c X_c prod (1 +- r) / 2
+// as seven coefficient vectors, and whether every node lies on it.  A node made
+// from the corners in double precision (products of two-term weights, eight
+// terms summed) is off by up to about six units of rounding of the largest
+// coordinate; eight count as on the map.
+__global__ __launch_bounds__(kGeoThreads) void straight_kernel(const double* __restrict__ xyz,
+                                                               const double* __restrict__ xi,
+                                                               int n1, double* __restrict__ geo,
+                                                               int* __restrict__ curved) {
+  const int64_t e = blockIdx.x;
+  const int P2 = n1 * n1, P = P2 * n1, h = n1 - 1;
+  const double* x = xyz + e * 3 * P;
+  double c[8][3];  // 1, r, s, t, rs, rt, st, rst
+  double size = 0.0;
+  for (int d = 0; d < 3; ++d) {
+    double X[2][2][2];
+    for (int k = 0; k < 2; ++k)
+      for (int j = 0; j < 2; ++j)
+        for (int i = 0; i < 2; ++i) {
+          X[k][j][i] = x[3 * (k * h * P2 + j * h * n1 + i * h) + d];
+          size = fmax(size, fabs(X[k][j][i]));
+        }
+    double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    for (int k = 0; k < 2; ++k)
+      for (int j = 0; j < 2; ++j)
+        for (int i = 0; i < 2; ++i) {
+          const double r = i ? 1.0 : -1.0, q = j ? 1.0 : -1.0, t = k ? 1.0 : -1.0, v = X[k][j][i];
+          s[0] += v;
+          s[1] += r * v;
+          s[2] += q * v;
+          s[3] += t * v;
+          s[4] += r * q * v;
+          s[5] += r * t * v;
+          s[6] += q * t * v;
+          s[7] += r * q * t * v;
+        }
+    for (int a = 0; a < 8; ++a) c[a][d] = 0.125 * s[a];
+  }
+  const double tol = 8.0 * 2.220446049250313e-16 * size;
+  int off = 0;
+  for (int q = threadIdx.x; q < P; q += blockDim.x) {
+    const double r = xi[q % n1], s = xi[(q / n1) % n1], t = xi[q / P2];
+    for (int d = 0; d < 3; ++d) {
+      const double v = c[0][d] + r * c[1][d] + s * c[2][d] + t * c[3][d] + r * s * c[4][d] +
+                       r * t * c[5][d] + s * t * c[6][d] + r * s * t * c[7][d];
+      if (!(fabs(v - x[3 * q + d]) <= tol)) off = 1;
+    }
+  }
+  if (__syncthreads_or(off) && threadIdx.x == 0) atomicAdd(curved, 1);
+  if (threadIdx.x < 21) geo[e * 21 + threadIdx.x] = c[1 + threadIdx.x / 3][threadIdx.x % 3];
+}
+
 }  // namespace
+
+hipError_t launch_straight(const sem_mesh* m, const double* xyz, double* geo, int* curved,
+                           hipStream_t s) {
+  // the nodes lie behind D and the weights in the D64 buffer (see sem_setup_mesh)
+  const double* xi = m->D64.as<double>() + m->n1 * m->n1 + m->n1;
+  hipLaunchKernelGGL(straight_kernel, dim3((unsigned)m->E), dim3(kGeoThreads), 0, s, xyz, xi,
+                     m->n1, geo, curved);
+  return hipGetLastError();
+}
 
 hipError_t launch_geometry(const sem_mesh* m, const double* xyz, double* G, double* B, float* G32,
                            float* B32, int* bad_count, hipStream_t s) {
