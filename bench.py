@@ -184,7 +184,7 @@ def ax_kernel_name(N):
 
 
 # the operator kernel's sources: the counter summary holds for them only
-OPERATOR_SOURCES = ("kernels_ax.hip", "common.hpp", "mfma_16x16x4.hpp")
+OPERATOR_SOURCES = ("kernels_ax.hip", "ax_tiles.hpp", "common.hpp", "mfma_16x16x4.hpp")
 
 
 def operator_sources_sha256():

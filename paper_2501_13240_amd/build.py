@@ -30,7 +30,7 @@ CFLAGS = [
 ]
 
 SOURCES = ["api.cpp", "host_setup.cpp", "kernels_ax.hip", "kernels_setup.hip",
-           "kernels_vec.hip", "solver.hip", "pmg.hip", "coarse.hip", "pmg_host.cpp", "schwarz_host.cpp",
+           "kernels_vec.hip", "solver.hip", "pmg.hip", "coarse.hip", "resident.hip", "pmg_host.cpp", "schwarz_host.cpp",
            "kernels_schwarz.hip", "kernels_adv.hip", "adv_host.cpp", "noalloc.hip"]
 
 

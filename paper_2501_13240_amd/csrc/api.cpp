@@ -392,6 +392,8 @@ static sem_status solve_free(const sem_mesh* m, const double* k, double h2,
   sem_status st = W.init(m, std::max(opts.max_iter, 1));
   if (st) return st;
   W.ev_used = 0;
+  W.resident_ms = 0.0;
+  W.resident_ax = 0;
   if (m->n_free == 0) {
     // no unknowns (every node Dirichlet): the solution is empty, so the
     // output holds 0 at every copy; no preconditioner is set up
@@ -653,8 +655,8 @@ static sem_status solve_free(const sem_mesh* m, const double* k, double h2,
       float d = 0.f;
       if (hipEventElapsedTime(&d, W.ev[i], W.ev[i + 1]) == hipSuccess) ax_ms += d;
     }
-    stats->ax_ms = ax_ms;
-    stats->ax_launches = W.ev_used / 2;
+    stats->ax_ms = ax_ms + W.resident_ms;
+    stats->ax_launches = W.ev_used / 2 + W.resident_ax;
   }
   if (fail_status == 2 || fail_status == 3)
     return fail(SEM_EBREAKDOWN, fail_status == 2 ? "CG breakdown: p.Ap <= 0"

@@ -92,7 +92,8 @@ struct CgScalars {
   double mean_w;    // null-space projection: mean of w over unique nodes
   double inv_n;     // 1 / n_free
   double zw;        // flexible CG: z.w
-  double pad[3];
+  double op_ticks;  // resident CG with profile: ticks spent in the operator
+  double pad[2];
   int32_t it;       // completed iterations
   int32_t done;     // 1 = converged or failed: every later kernel of the solve is a no-op
   int32_t status;   // 0 ok, 1 converged, 2 breakdown, 3 non-finite
@@ -105,7 +106,7 @@ struct CgScalars {
   int32_t pending;  // 1 = x += alpha p of iteration kcur still to apply (set by the
                     // residual update, cleared by the next segmented sum; applied by
                     // the direction update)
-  int32_t pad2;
+  int32_t gave_up;  // 1 = a wait between workgroups of the resident CG gave up
 };
 
 // Workgroups are dispatched round-robin over the 8 XCDs (workgroup b runs on

@@ -69,29 +69,32 @@ __device__ __forceinline__ void group_sum2(double& a, double& b, double* red) {
   }
 }
 
-// a, b <- their sums over all workgroups; also a barrier between them that
-// orders store_shared() before load_shared().  False when a wait gave up
-// (the same on every thread of the workgroup).  `slots`: 2 x nblk x
-// kGridWords words.
+// First half of an exchange: a, b <- their sums over the workgroup, published
+// in its slot.  `slots`: 2 x nblk x kGridWords words.
 template <int NW>
-__device__ __forceinline__ bool grid_sum2(double& a, double& b, uint32_t tag, int nblk,
+__device__ __forceinline__ void grid_put2(double& a, double& b, uint32_t tag, int nblk,
                                           uint64_t* __restrict__ slots, double* red) {
-  // this wavefront's shared stores have reached the device's memory before
-  // the workgroup publishes
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_s_waitcnt(0);
   group_sum2<NW>(a, b, red);
-  if (nblk == 1) return true;
+  if (nblk == 1) return;
   uint64_t* set = slots + (size_t)(tag & 1) * nblk * kGridWords;
-  const uint64_t hi = (uint64_t)tag << 32;
   if (threadIdx.x < kGridWords) {
     const double v = threadIdx.x < 2 ? a : b;
     const uint32_t half =
         (uint32_t)((threadIdx.x & 1) ? __double2hiint(v) : __double2loint(v));
-    grid_store(set + (size_t)blockIdx.x * kGridWords + threadIdx.x, hi | half);
+    grid_store(set + (size_t)blockIdx.x * kGridWords + threadIdx.x, (uint64_t)tag << 32 | half);
   }
+}
+
+// Second half: a, b <- the sums over all workgroups.  False when a wait gave
+// up, here or before (`gave_up`, on any thread): the same on every thread of
+// the workgroup.
+template <int NW>
+__device__ __forceinline__ bool grid_get2(double& a, double& b, uint32_t tag, int nblk,
+                                          const uint64_t* __restrict__ slots, double* red,
+                                          int gave_up) {
+  if (nblk == 1) return !__syncthreads_or(gave_up);
+  const uint64_t* set = slots + (size_t)(tag & 1) * nblk * kGridWords;
   double ta = 0.0, tb = 0.0;
-  int gave_up = 0;
   for (int s = threadIdx.x; s < nblk; s += NW * 64) {
     const uint64_t* q = set + (size_t)s * kGridWords;
     uint64_t w0, w1, w2, w3;
@@ -101,8 +104,8 @@ __device__ __forceinline__ bool grid_sum2(double& a, double& b, uint32_t tag, in
       w1 = grid_load(q + 1);
       w2 = grid_load(q + 2);
       w3 = grid_load(q + 3);
-      if (((w0 ^ hi) >> 32) == 0 && ((w1 ^ hi) >> 32) == 0 && ((w2 ^ hi) >> 32) == 0 &&
-          ((w3 ^ hi) >> 32) == 0)
+      if ((uint32_t)(w0 >> 32) == tag && (uint32_t)(w1 >> 32) == tag &&
+          (uint32_t)(w2 >> 32) == tag && (uint32_t)(w3 >> 32) == tag)
         break;
       if (++spin >= kGridSpinLimit) {
         gave_up = 1;
@@ -118,5 +121,61 @@ __device__ __forceinline__ bool grid_sum2(double& a, double& b, uint32_t tag, in
   group_sum2<NW>(a, b, red);
   return true;
 }
+
+// a, b <- their sums over all workgroups; also a barrier between them that
+// orders store_shared() before load_shared().
+template <int NW>
+__device__ __forceinline__ bool grid_sum2(double& a, double& b, uint32_t tag, int nblk,
+                                          uint64_t* __restrict__ slots, double* red) {
+  // this wavefront's shared stores have reached the device's memory before
+  // the workgroup publishes
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_s_waitcnt(0);
+  grid_put2<NW>(a, b, tag, nblk, slots, red);
+  return grid_get2<NW>(a, b, tag, nblk, slots, red, 0);
+}
+
+// Single values handed from workgroup to workgroup without an exchange: the
+// words carry the tag, as the slots do, so a reader waits for the value
+// itself.  A place may be written again once an exchange lies between the
+// reads of its old value and the new write.
+template <typename T>
+constexpr int kTagWords = sizeof(T) / 4;
+
+template <typename T>
+__device__ __forceinline__ void put_tagged(uint64_t* __restrict__ at, T v, uint32_t tag) {
+  const uint64_t hi = (uint64_t)tag << 32;
+  if constexpr (sizeof(T) == 8) {
+    grid_store(at, hi | (uint32_t)__double2loint(v));
+    grid_store(at + 1, hi | (uint32_t)__double2hiint(v));
+  } else {
+    grid_store(at, hi | (uint32_t)__float_as_int(v));
+  }
+}
+
+template <typename T>
+struct Tagged {
+  uint64_t w[kTagWords<T>];
+  __device__ __forceinline__ void load(const uint64_t* __restrict__ at) {
+#pragma unroll
+    for (int i = 0; i < kTagWords<T>; ++i) w[i] = grid_load(at + i);
+  }
+  __device__ __forceinline__ bool has(uint32_t tag) const {
+    bool ok = true;
+#pragma unroll
+    for (int i = 0; i < kTagWords<T>; ++i) ok = ok && (uint32_t)(w[i] >> 32) == tag;
+    return ok;
+  }
+  // waits for the value (the first load may have been issued before)
+  __device__ __forceinline__ T get(const uint64_t* __restrict__ at, uint32_t tag, int& gave_up) {
+    for (int spin = 0; !has(tag); load(at))
+      if (++spin >= kGridSpinLimit) {
+        gave_up = 1;
+        break;
+      }
+    if constexpr (sizeof(T) == 8) return __hiloint2double((int)(uint32_t)w[1], (int)(uint32_t)w[0]);
+    else return __int_as_float((int)(uint32_t)w[0]);
+  }
+};
 
 }  // namespace sem

@@ -26,6 +26,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "resident.hpp"
 #include "solver.hpp"
 
 namespace sem {
@@ -1101,6 +1102,10 @@ template sem_status cheb_apply_bufs<double, float>(const sem_mesh*, const Op<flo
 
 // ------------------------------------------------------------------- CG
 
+// iterations per launch of the resident CG: a launch ends within milliseconds,
+// and the next one's start (about 20 us with the read-back) is lost in them
+constexpr int kResidentIters = 512;
+
 template <typename T, typename Tp>
 sem_status cg_solve(const sem_mesh* m, SolveWork& W, const CgArgs<T, Tp>& a, CgResult& res,
                     hipStream_t s) {
@@ -1239,6 +1244,23 @@ sem_status cg_solve(const sem_mesh* m, SolveWork& W, const CgArgs<T, Tp>& a, CgR
                        partC, (int)nb, sc, bhist);
     return SEM_OK;
   };
+  // the result from the scalars read back, and the histories
+  auto finish = [&]() -> sem_status {
+    res.iters = h.it;
+    res.applies += h.it + (jac ? 0 : h.it * (a.cheb_order - 1));
+    res.rnorm = std::sqrt(h.rr);
+    res.status = h.status;
+    res.converged = (h.status == 1) || (a.fixed && h.rr <= tol2);
+    if (a.hist && h.it > 0)
+      SEM_HIP(hipMemcpy(a.hist + 1, hist + 1, h.it * sizeof(double), hipMemcpyDeviceToHost));
+    if (a.alpha_out && h.it > 0) {
+      a.alpha_out->resize(h.it);
+      a.beta_out->resize(h.it);
+      SEM_HIP(hipMemcpy(a.alpha_out->data(), ahist, h.it * sizeof(double), hipMemcpyDeviceToHost));
+      SEM_HIP(hipMemcpy(a.beta_out->data(), bhist, h.it * sizeof(double), hipMemcpyDeviceToHost));
+    }
+    return SEM_OK;
+  };
   auto iteration = [&](hipStream_t ss) -> sem_status {
     sem_status e;
     if (split && jac) {
@@ -1290,6 +1312,34 @@ sem_status cg_solve(const sem_mesh* m, SolveWork& W, const CgArgs<T, Tp>& a, CgR
     SEM_CHECK_LAUNCH("CG iteration");
     return SEM_OK;
   };
+
+  if (jac && op_it.lp == 0 && a.max_it > 0 && nf <= graph_max_free() && resident_fits<T>(m)) {
+    // a small mesh: all iterations in one kernel, up to kResidentIters a launch
+    ResidentArgs<T> ra;
+    ra.op = a.op;
+    ra.x = x;
+    ra.z = r;  // r holds z = S r here
+    ra.p = p;
+    ra.dinv = a.dinv;
+    ra.profile = a.profile;
+    if ((st = resident_begin(m, W, s))) return st;
+    for (int enq = 0; enq < a.max_it; enq += kResidentIters) {
+      if ((st = resident_run<T>(m, W, ra, kResidentIters, s))) return st;
+      if (a.fixed && enq + kResidentIters < a.max_it) continue;
+      SEM_HIP(hipMemcpyAsync(&W.h_sc[0], sc, sizeof(CgScalars), hipMemcpyDeviceToHost, s));
+      SEM_HIP(hipStreamSynchronize(s));
+      if (W.h_sc[0].done) break;
+    }
+    h = W.h_sc[0];
+    if (h.gave_up) return fail(SEM_EDEVICE, "resident CG: a workgroup did not answer");
+    if (a.profile) {
+      int khz = 0;
+      SEM_HIP(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, m->device));
+      W.resident_ms += khz > 0 ? h.op_ticks / khz : 0.0;
+      W.resident_ax += h.it;
+    }
+    return finish();
+  }
 
   // Iterations between convergence read-backs; one chunk is always queued
   // ahead of the one being polled, and kernels of a finished solve return at
@@ -1392,20 +1442,7 @@ sem_status cg_solve(const sem_mesh* m, SolveWork& W, const CgArgs<T, Tp>& a, CgR
     SEM_HIP(hipMemcpy(&W.h_sc[0], sc, sizeof(CgScalars), hipMemcpyDeviceToHost));
     h = W.h_sc[0];
   }
-  res.iters = h.it;
-  res.applies += h.it + (jac ? 0 : h.it * (a.cheb_order - 1));
-  res.rnorm = std::sqrt(h.rr);
-  res.status = h.status;
-  res.converged = (h.status == 1) || (a.fixed && h.rr <= tol2);
-  if (a.hist && h.it > 0)
-    SEM_HIP(hipMemcpy(a.hist + 1, hist + 1, h.it * sizeof(double), hipMemcpyDeviceToHost));
-  if (a.alpha_out && h.it > 0) {
-    a.alpha_out->resize(h.it);
-    a.beta_out->resize(h.it);
-    SEM_HIP(hipMemcpy(a.alpha_out->data(), ahist, h.it * sizeof(double), hipMemcpyDeviceToHost));
-    SEM_HIP(hipMemcpy(a.beta_out->data(), bhist, h.it * sizeof(double), hipMemcpyDeviceToHost));
-  }
-  return SEM_OK;
+  return finish();
 }
 template sem_status cg_solve<double, double>(const sem_mesh*, SolveWork&, const CgArgs<double, double>&,
                                              CgResult&, hipStream_t);

@@ -17,10 +17,13 @@ struct SolveWork {
   DevBuf cwf, cza, cz;                               // fused Chebyshev: A d at single-copy
                                                      // nodes, running z, output z
   DevBuf part, sc, red, hist, ahist, bhist, epart;
+  DevBuf rsync;                                      // resident CG: exchange slots, tag
   CgScalars* h_sc = nullptr;  // pinned: [0..1] polling slots, [3] upload
   double* h_red = nullptr;    // pinned reduction results
   std::vector<hipEvent_t> ev; // profiling events
   int ev_used = 0;
+  double resident_ms = 0.0;   // the same of a resident CG: time in its operator phases
+  int resident_ax = 0;        // and their number
   hipStream_t cap = nullptr;  // stream used only to capture iteration graphs
   ~SolveWork();
   sem_status capture_stream(hipStream_t* out);
