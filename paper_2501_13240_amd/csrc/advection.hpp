@@ -12,9 +12,14 @@ namespace sem {
 // one quadrature rule's factors on a mesh
 struct AdvRule {
   int q1 = 0;             // points per direction
-  DevBuf mats64, mats32;  // J [q1][n], JD = J D [q1][n], J^T [n][q1]
-  DevBuf eo64, eo32;      // 3/2 rule: even and odd halves of J, JD and J^T (see Eo)
-  DevBuf G64, G32;        // [E][9][q1^3]: w detJ dr_a/dx_d in slot 3 a + d
+  DevBuf mats64;      // J [q1][n], JD = J D [q1][n], J^T [n][q1]
+  DevBuf eo64, eo32;  // even and odd halves of J, JD and J^T (see Eo), points x, weights w
+  DevBuf pts64;       // x [q1], w [q1]
+  DevBuf G64, G32;    // [E][9][q1^3]: w detJ dr_a/dx_d in slot 3 a + d
+  // every element is the trilinear image of its corners up to rounding; geo
+  // [E][21]: its coefficients (see launch_straight)
+  bool straight = false;
+  DevBuf geo;
 };
 
 // points per direction of a rule (0: collocation, 1: 3/2 rule)
@@ -33,10 +38,10 @@ hipError_t launch_adv_geometry(const sem_mesh* m, int q1, const double* mats, co
                                hipStream_t s);
 
 // out[k][e] = C_e(u) f[k] for every element and each of nf fields: u DEVICE
-// [3][E][P], f and out [nf][E][P]; rule 0 reads D (DEVICE [n][n]) and G
-// [E][9][P], rule 1 eo and G [E][9][q1^3]
+// [3][E][P], f and out [nf][E][P]; rule 0 reads D (DEVICE [n][n]), rule 1 R's
+// eo; both the factors of R, or the elements' coefficients where it is straight
 template <typename T>
-hipError_t launch_advect(const sem_mesh* m, int rule, int nf, const T* eo, const T* D,
-                         const T* G, const T* u, const T* f, T* out, hipStream_t s);
+hipError_t launch_advect(const sem_mesh* m, const AdvRule& R, int rule, int nf, const T* D,
+                         const T* u, const T* f, T* out, hipStream_t s);
 
 }  // namespace sem

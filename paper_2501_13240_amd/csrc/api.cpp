@@ -1154,7 +1154,6 @@ sem_status sem_setup_advection(sem_mesh* m, const sem_mesh_desc* desc, int32_t r
       JD[i * n + j] = acc;
       JT[j * q1 + i] = J[i * n + j];
     }
-  std::vector<float> mats32(mats.begin(), mats.end());
   std::unique_ptr<AdvRule> R(new AdvRule());
   R->q1 = q1;
   // even and odd halves (A_ij +- A_i,NI-1-j) / 2 of the first half of the rows
@@ -1171,28 +1170,35 @@ sem_status sem_setup_advection(sem_mesh* m, const sem_mesh_desc* desc, int32_t r
   halves(mats.data(), q1, n);
   halves(JD, q1, n);
   halves(JT, n, q1);
+  std::vector<double> pts(x);
+  pts.insert(pts.end(), w.begin(), w.end());
+  eo.insert(eo.end(), pts.begin(), pts.end());
   const std::vector<float> eo32(eo.begin(), eo.end());
-  if ((st = upload(R->mats64, mats, s)) || (st = upload(R->mats32, mats32, s)) ||
+  if ((st = upload(R->mats64, mats, s)) || (st = upload(R->pts64, pts, s)) ||
       (st = upload(R->eo64, eo, s)) || (st = upload(R->eo32, eo32, s)) ||
+      (st = R->geo.ensure((size_t)m->E * 21 * sizeof(double))) ||
       (st = R->G64.ensure((size_t)m->E * 9 * Q * sizeof(double))) ||
       (st = R->G32.ensure((size_t)m->E * 9 * Q * sizeof(float))))
     return st;
   DevBuf dxyz, dw, dbad;
   if ((st = dxyz.ensure((size_t)3 * m->nL * sizeof(double))) || (st = upload(dw, w, s)) ||
-      (st = dbad.ensure(sizeof(int))))
+      (st = dbad.ensure(2 * sizeof(int))))
     return st;
   SEM_HIP(hipMemcpyAsync(dxyz.p, desc->xyz, (size_t)3 * m->nL * sizeof(double),
                          hipMemcpyHostToDevice, s));
-  SEM_HIP(launch_fill<int>(dbad.as<int>(), 1, 0, s));
+  SEM_HIP(launch_fill<int>(dbad.as<int>(), 2, 0, s));
+  SEM_HIP(launch_straight(m, dxyz.as<double>(), R->geo.as<double>(), dbad.as<int>() + 1, s));
   SEM_HIP(launch_adv_geometry(m, q1, R->mats64.as<double>(), dw.as<double>(),
                               dxyz.as<double>(), R->G64.as<double>(), R->G32.as<float>(),
                               dbad.as<int>(), s));
-  int bad = 0;
-  SEM_HIP(hipMemcpyAsync(&bad, dbad.p, sizeof(int), hipMemcpyDeviceToHost, s));
+  int flags[2] = {0, 0};
+  SEM_HIP(hipMemcpyAsync(flags, dbad.p, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
   SEM_HIP(hipStreamSynchronize(s));
-  if (bad > 0)
+  if (flags[0] > 0)
     return fail(SEM_EINVAL, "element map is not orientation-preserving (detJ <= 0) at " +
-                                std::to_string(bad) + " quadrature points");
+                                std::to_string(flags[0]) + " quadrature points");
+  R->straight = flags[1] == 0;
+  if (!R->straight) R->geo.release();
   delete m->adv[rule];
   m->adv[rule] = R.release();
   return SEM_OK;
@@ -1232,13 +1238,11 @@ sem_status sem_advect_fields(const sem_mesh* m, int32_t rule, const void* u, int
   hipStream_t s = (hipStream_t)stream;
   hipError_t e;
   if (prec == SEM_FP64)
-    e = launch_advect<double>(m, rule, nf, R->eo64.as<double>(), m->D64.as<double>(),
-                              R->G64.as<double>(), (const double*)u, (const double*)f,
-                              (double*)out, s);
+    e = launch_advect<double>(m, *R, rule, nf, m->D64.as<double>(), (const double*)u,
+                              (const double*)f, (double*)out, s);
   else
-    e = launch_advect<float>(m, rule, nf, R->eo32.as<float>(), m->D32.as<float>(),
-                             R->G32.as<float>(), (const float*)u, (const float*)f, (float*)out,
-                             s);
+    e = launch_advect<float>(m, *R, rule, nf, m->D32.as<float>(), (const float*)u,
+                             (const float*)f, (float*)out, s);
   if (e != hipSuccess) return hip_fail(e, "advect");
   return SEM_OK;
 }

@@ -17,7 +17,7 @@
 #include <type_traits>
 
 #include "advection.hpp"
-#include "mfma_16x16x4.hpp"
+#include "ax_tiles.hpp"
 
 namespace sem {
 namespace {
@@ -203,6 +203,35 @@ struct AdvShape {
   static_assert(2 * A >= Y && 3 * n2 <= 3 * TPB, "regions");
 };
 
+// Factors w adj_ad, a = 0, 1, 2, of velocity component d along the line (r, s, z)
+// of an element with the coefficient vectors g = (x_r, x_s, x_t, x_rs, x_rt,
+// x_st, x_rst): c0 + c1 z, c2 + c3 z and c4 + c5 z + c6 z^2, the components of
+// x_s x x_t, x_t x x_r and x_r x x_s, where x_r = a0 + a1 z and x_s = b0 + b1 z,
+// and x_t = h is the same all along it.  Formed in FP64, rounded to T once.
+template <typename T>
+__device__ __forceinline__ void line_factors(UniformD g, int d, double r, double s, double w,
+                                             T (&c)[7]) {
+  const int e = (d + 1) % 3, f = (d + 2) % 3;
+  double a0[2], a1[2], b0[2], b1[2], h[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int x = i ? f : e;
+    a0[i] = g[x] + g[9 + x] * s;
+    a1[i] = g[12 + x] + g[18 + x] * s;
+    b0[i] = g[3 + x] + g[9 + x] * r;
+    b1[i] = g[15 + x] + g[18 + x] * r;
+    h[i] = (g[6 + x] + g[12 + x] * r) + (g[15 + x] + g[18 + x] * r) * s;
+  }
+  auto cross = [](const double (&p)[2], const double (&q)[2]) { return p[0] * q[1] - p[1] * q[0]; };
+  c[0] = (T)(w * cross(b0, h));
+  c[1] = (T)(w * cross(b1, h));
+  c[2] = (T)(w * cross(h, a0));
+  c[3] = (T)(w * cross(h, a1));
+  c[4] = (T)(w * cross(a0, b0));
+  c[5] = (T)(w * (cross(a0, b1) + cross(a1, b0)));
+  c[6] = (T)(w * cross(a1, b1));
+}
+
 // Over-integrated rule, one element per workgroup; a thread transforms one
 // line at a time in registers:
 //   u_d:  along j from memory, along i through LDS, along k into the M^3
@@ -227,11 +256,24 @@ struct AdvShape {
 //   10     282/558 -> 194/304            252/510 -> 87/146
 // (Requesting a component's factors ahead into registers, as that form did,
 // costs occupancy here: 774 against 322 us.)
-template <int N, typename T>
+//
+// GEO 1 (every element straight-edged): the factors along the thread's point
+// line are polynomials of its coordinate (line_factors), evaluated in place of
+// nine streamed values.  The same boxes, stored -> formed:
+//   N      FP64                          FP32
+//   3      225/311 -> 113/258            111/139 -> 71/136
+//   5      226/326 -> 113/233            111/152 -> 63/122
+//   7      211/326 -> 111/250            107/163 -> 63/134
+//   9      274/423 -> 129/295            117/173 -> 65/140
+//   10     194/302 -> 105/235            89/145 -> 55/122
+// bound by its vector instructions throughout.  (N = 7, FP64: 171 registers
+// leave two waves per SIMD, 167/379 us, hence the budget of three.)
+template <int N, typename T, int GEO>
 __global__ __launch_bounds__((AdvShape<N, T>::TPB))
-    __attribute__((amdgpu_waves_per_eu(N == 8 && sizeof(T) == 8 ? 3 : 1))) void adv_dealias_kernel(
-    int nf, const T* __restrict__ coef, const T* __restrict__ G, const T* __restrict__ u,
-    int64_t ustride, const T* __restrict__ f, T* __restrict__ out) {
+    __attribute__((amdgpu_waves_per_eu((N == 8 || (N == 7 && GEO)) && sizeof(T) == 8 ? 3 : 1))) void adv_dealias_kernel(
+    int nf, const T* __restrict__ coef, const T* __restrict__ G, const double* __restrict__ geo,
+    const double* __restrict__ pts, const T* __restrict__ u, int64_t ustride,
+    const T* __restrict__ f, T* __restrict__ out) {
   typedef AdvShape<N, T> S;
   typedef typename S::J J;
   typedef typename S::JD JD;
@@ -243,9 +285,12 @@ __global__ __launch_bounds__((AdvShape<N, T>::TPB))
   const T* cJ = coef;
   const T* cJD = coef + J::SZ;
   const T* cJT = cJD + JD::SZ;
+  const T* cP = cJT + JT::SZ;  // points, weights
+  (void)cP;
   const int t = threadIdx.x;
   const int64_t eP = (int64_t)blockIdx.x * P;
   const T* Ge = G + (int64_t)blockIdx.x * 9 * Q;
+  (void)Ge;
   // this thread's node line along j (p = k n + i), its row of lines along i
   // and its point line along k
   const bool own_j = t < n2, own_k = t < M2;
@@ -279,12 +324,25 @@ __global__ __launch_bounds__((AdvShape<N, T>::TPB))
     J([&](int i) { return src[r * SA + i]; }).apply(cJ, [&](int q, T y) { dst[r * SY + q] = y; });
   };
   auto add_v = [&](int d, const T* __restrict__ src) {
-    const T* g = Ge + d * Q + t;
-    J([&](int k) { return src[ybase + k * M * SY]; }).apply(cJ, [&](int q, T y) {
+    auto line = [&](int k) { return src[ybase + k * M * SY]; };
+    if constexpr (GEO == 1) {
+      T c[7];
+      line_factors<T>((UniformD)(uintptr_t)(geo + (int64_t)blockIdx.x * 21), d, pts[t % M],
+                      pts[t / M], pts[M + t % M] * pts[M + t / M], c);
+      J(line).apply(cJ, [&](int q, T y) {
+        const T z = cP[q], wy = cP[M + q] * y;
+        V[0][q] += (c[0] + c[1] * z) * wy;
+        V[1][q] += (c[2] + c[3] * z) * wy;
+        V[2][q] += (c[4] + (c[5] + c[6] * z) * z) * wy;
+      });
+    } else {
+      const T* g = Ge + d * Q + t;
+      J(line).apply(cJ, [&](int q, T y) {
 #pragma unroll
-      for (int a = 0; a < 3; ++a)
-        V[a][q] += __builtin_nontemporal_load(g + 3 * a * Q + q * M2) * y;
-    });
+        for (int a = 0; a < 3; ++a)
+          V[a][q] += __builtin_nontemporal_load(g + 3 * a * Q + q * M2) * y;
+      });
+    }
   };
   if constexpr (NY == 3) {
     for (int p = t; p < 3 * n2; p += TPB) lines_j(p / n2, p % n2, sA + (p / n2) * S::A);
@@ -379,10 +437,16 @@ __global__ __launch_bounds__((AdvShape<N, T>::TPB))
   }
 }
 
-template <int N, typename T>
+// Collocation rule, one element per workgroup, a thread per node.  Bound by its
+// stream with stored factors (GEO 0) and by the derivative sums' LDS reads with
+// straight-edged ones, which it forms at its nodes (GEO 1; boxes of 4 million
+// points, one / four fields in FP64, us: N = 3 101/173 -> 58/156, 7 85/140 ->
+// 39/115, 10 103/192 -> 49/167).
+template <int N, typename T, int GEO>
 __global__ __launch_bounds__(kAdvThreads) void adv_colloc_kernel(
-    int nf, const T* __restrict__ D, const T* __restrict__ G, const T* __restrict__ u,
-    int64_t ustride, const T* __restrict__ f, T* __restrict__ out) {
+    int nf, const T* __restrict__ D, const T* __restrict__ G, const double* __restrict__ geo,
+    const double* __restrict__ pts, const T* __restrict__ u, int64_t ustride,
+    const T* __restrict__ f, T* __restrict__ out) {
   constexpr int n = N + 1, P = n * n * n, PT = (P + kAdvThreads - 1) / kAdvThreads;
   __shared__ T sF[P];
   __shared__ T sD[n * n];
@@ -396,13 +460,25 @@ __global__ __launch_bounds__(kAdvThreads) void adv_colloc_kernel(
     const int q = threadIdx.x + j * kAdvThreads;
 #pragma unroll
     for (int a = 0; a < 3; ++a) V[j][a] = T(0);
-    if (q < P)
+    if (q < P) {
+      const int i = q % n, jj = (q / n) % n, kk = q / (n * n);
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
         const T ud = u[d * ustride + e * P + q];
+        if constexpr (GEO == 1) {
+          const double z = pts[kk];
+          double cd[7];
+          line_factors<double>((UniformD)(uintptr_t)(geo + e * 21), d, pts[i], pts[jj],
+                               pts[n + i] * pts[n + jj] * pts[n + kk], cd);
+          V[j][0] += (T)(cd[0] + cd[1] * z) * ud;
+          V[j][1] += (T)(cd[2] + cd[3] * z) * ud;
+          V[j][2] += (T)(cd[4] + (cd[5] + cd[6] * z) * z) * ud;
+        } else {
 #pragma unroll
-        for (int a = 0; a < 3; ++a) V[j][a] += Ge[(3 * a + d) * P + q] * ud;
+          for (int a = 0; a < 3; ++a) V[j][a] += Ge[(3 * a + d) * P + q] * ud;
+        }
       }
+    }
   }
   for (int k = 0; k < nf; ++k) {
     if (k > 0) __syncthreads();  // the previous field's sums are done with sF
@@ -506,16 +582,37 @@ __global__ void adv_metric_finish(int64_t E, int q1, const double* __restrict__ 
 }
 
 template <int N, typename T>
-hipError_t run_advect(const sem_mesh* m, int rule, int nf, const T* eo, const T* D, const T* G,
+hipError_t run_advect(const sem_mesh* m, const AdvRule& R, int rule, int nf, const T* D,
                       const T* u, const T* f, T* out, hipStream_t s) {
   const int64_t ustride = m->E * (int64_t)m->P;
-  if (rule == 0) {
-    hipLaunchKernelGGL((adv_colloc_kernel<N, T>), dim3((unsigned)m->E), dim3(kAdvThreads), 0, s,
-                       nf, D, G, u, ustride, f, out);
-    return hipGetLastError();
+  const T* G = nullptr;
+  const T* eo = nullptr;
+  if constexpr (sizeof(T) == 8) {
+    G = R.G64.as<double>();
+    eo = R.eo64.as<double>();
+  } else {
+    G = R.G32.as<float>();
+    eo = R.eo32.as<float>();
   }
-  hipLaunchKernelGGL((adv_dealias_kernel<N, T>), dim3((unsigned)m->E),
-                     dim3(AdvShape<N, T>::TPB), 0, s, nf, eo, G, u, ustride, f, out);
+  const double* geo = R.geo.as<double>();
+  const double* pts = R.pts64.as<double>();
+  const dim3 grid((unsigned)m->E);
+  // straight-edged: from N = 3 on (box of 4 million points, one / four fields, us,
+  // stored -> formed: N = 2 FP64 259/358 -> 166/373, FP32 97/193 -> 119/212;
+  // N = 3 FP64 223/309 -> 113/258, FP32 108/146 -> 71/136), collocation always
+  constexpr int kFrom = 3;
+#define SEM_ADV(KERNEL, TPB, MAT, FROM)                                                        \
+  do {                                                                                         \
+    if (N >= FROM && R.straight)                                                               \
+      hipLaunchKernelGGL((KERNEL<N, T, (N >= FROM ? 1 : 0)>), grid, dim3(TPB), 0, s, nf, MAT, G, geo, pts, u,    \
+                         ustride, f, out);                                                     \
+    else                                                                                       \
+      hipLaunchKernelGGL((KERNEL<N, T, 0>), grid, dim3(TPB), 0, s, nf, MAT, G, geo, pts, u,    \
+                         ustride, f, out);                                                     \
+  } while (0)
+  if (rule == 0) SEM_ADV(adv_colloc_kernel, kAdvThreads, D, 1);
+  else SEM_ADV(adv_dealias_kernel, (AdvShape<N, T>::TPB), eo, kFrom);
+#undef SEM_ADV
   return hipGetLastError();
 }
 
@@ -562,28 +659,27 @@ hipError_t launch_adv_geometry(const sem_mesh* m, int q1, const double* mats, co
 }
 
 template <typename T>
-hipError_t launch_advect(const sem_mesh* m, int rule, int nf, const T* eo, const T* D,
-                         const T* G, const T* u, const T* f, T* out, hipStream_t s) {
+hipError_t launch_advect(const sem_mesh* m, const AdvRule& R, int rule, int nf, const T* D,
+                         const T* u, const T* f, T* out, hipStream_t s) {
   if (nf <= 0) return hipSuccess;
   switch (m->N) {
-    case 1: return run_advect<1, T>(m, rule, nf, eo, D, G, u, f, out, s);
-    case 2: return run_advect<2, T>(m, rule, nf, eo, D, G, u, f, out, s);
-    case 3: return run_advect<3, T>(m, rule, nf, eo, D, G, u, f, out, s);
-    case 4: return run_advect<4, T>(m, rule, nf, eo, D, G, u, f, out, s);
-    case 5: return run_advect<5, T>(m, rule, nf, eo, D, G, u, f, out, s);
-    case 6: return run_advect<6, T>(m, rule, nf, eo, D, G, u, f, out, s);
-    case 7: return run_advect<7, T>(m, rule, nf, eo, D, G, u, f, out, s);
-    case 8: return run_advect<8, T>(m, rule, nf, eo, D, G, u, f, out, s);
-    case 9: return run_advect<9, T>(m, rule, nf, eo, D, G, u, f, out, s);
-    case 10: return run_advect<10, T>(m, rule, nf, eo, D, G, u, f, out, s);
+    case 1: return run_advect<1, T>(m, R, rule, nf, D, u, f, out, s);
+    case 2: return run_advect<2, T>(m, R, rule, nf, D, u, f, out, s);
+    case 3: return run_advect<3, T>(m, R, rule, nf, D, u, f, out, s);
+    case 4: return run_advect<4, T>(m, R, rule, nf, D, u, f, out, s);
+    case 5: return run_advect<5, T>(m, R, rule, nf, D, u, f, out, s);
+    case 6: return run_advect<6, T>(m, R, rule, nf, D, u, f, out, s);
+    case 7: return run_advect<7, T>(m, R, rule, nf, D, u, f, out, s);
+    case 8: return run_advect<8, T>(m, R, rule, nf, D, u, f, out, s);
+    case 9: return run_advect<9, T>(m, R, rule, nf, D, u, f, out, s);
+    case 10: return run_advect<10, T>(m, R, rule, nf, D, u, f, out, s);
     default: return hipErrorInvalidValue;
   }
 }
-template hipError_t launch_advect<double>(const sem_mesh*, int, int, const double*,
-                                          const double*, const double*, const double*,
-                                          const double*, double*, hipStream_t);
-template hipError_t launch_advect<float>(const sem_mesh*, int, int, const float*, const float*,
-                                         const float*, const float*, const float*, float*,
-                                         hipStream_t);
+template hipError_t launch_advect<double>(const sem_mesh*, const AdvRule&, int, int,
+                                          const double*, const double*, const double*, double*,
+                                          hipStream_t);
+template hipError_t launch_advect<float>(const sem_mesh*, const AdvRule&, int, int, const float*,
+                                         const float*, const float*, float*, hipStream_t);
 
 }  // namespace sem
