@@ -9,9 +9,11 @@
 // eight elements -- and a thread keeps one row, its 27 columns' direction
 // values and its entries of x, r, p in registers over all iterations.  Each
 // iteration is two exchanges between the workgroups (p.Ap; r.z together with
-// z at the neighbours), 2.7-3 us each at 60 workgroups (see gridsync.hpp):
-// 222 us per V-cycle on that box, the p-multigrid solve to 1e-12 there 52.96
-// -> 47.90 ms.
+// z at the neighbours), about 2.5 us each at 60 workgroups (see gridsync.hpp):
+// 160 us per V-cycle on that box, the p-multigrid solve to 1e-12 there 52.7
+// -> 47.9 ms with it alone.  (Reading z after the exchange, all 27 columns by
+// every row, took 214 us; 140 unknowns in one workgroup took 96 us that way, 45
+// with z in LDS.)
 #include <algorithm>
 #include <vector>
 
@@ -53,35 +55,66 @@ __device__ __forceinline__ bool finite(double x) {
 // `iters` Jacobi-PCG iterations from x = 0 for b (minus its mean when
 // `neumann`), the recurrences of cg_fixed_device: p = z + beta p is formed by
 // the owner of a row and, with the same operands, by every row that has it as
-// a column.  A breakdown ends the iterations with the last x, a wait that
-// gave up (gridsync.hpp) writes NaN.
+// a column.  A workgroup's columns (its list, each once) come to LDS as tagged
+// values, waited for beside the partial sums; a single workgroup has them there
+// already.  A breakdown ends the iterations with the last x, a wait that gave up
+// (gridsync.hpp) writes NaN.
 template <typename T>
 __global__ __launch_bounds__(kCT)
     __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 3))) void k_coarse_cg(
     int nf, const T* __restrict__ val, const int32_t* __restrict__ col,
-    const T* __restrict__ dinv, const T* __restrict__ b, T* __restrict__ x, T* __restrict__ zx,
-    int iters, int neumann, double inv_n, uint64_t* __restrict__ slots,
-    uint32_t* __restrict__ epoch, const CgScalars* __restrict__ outer) {
+    const int32_t* __restrict__ list, const int32_t* __restrict__ nlist,
+    const T* __restrict__ dinv, const T* __restrict__ b, T* __restrict__ x,
+    uint64_t* __restrict__ zx, int iters, int neumann, double inv_n,
+    uint64_t* __restrict__ slots, uint32_t* __restrict__ epoch,
+    const CgScalars* __restrict__ outer) {
   if (outer && outer->done) return;  // uniform over the grid
+  constexpr int KW = kTagWords<T>;
+  constexpr int kBatch = 4;  // values a lane waits for together
   __shared__ double red[2 * kCN];
+  __shared__ T zl[kCT * kCW];
   const int nblk = gridDim.x;
   const int g = blockIdx.x * kCT + threadIdx.x;
   const bool act = g < nf;
   const uint32_t first = __hip_atomic_load(epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   uint32_t tag = first;
+  const int32_t* const mine = list + (int64_t)blockIdx.x * (kCT * kCW);
+  const int nl = nlist[blockIdx.x];
   T v[kCW], pn[kCW];
-  uint32_t c[kCW];  // byte offsets of the columns in zx
+  int32_t c[kCW];  // places of the columns in zl
 #pragma unroll
   for (int j = 0; j < kCW; ++j) {
     v[j] = act ? val[(int64_t)j * nf + g] : T(0);
-    c[j] = act ? (uint32_t)col[(int64_t)j * nf + g] * (uint32_t)sizeof(T) : 0u;
+    c[j] = act ? col[(int64_t)j * nf + g] : 0;
   }
-  const auto z_at = [&](uint32_t at) {
-    return load_shared(reinterpret_cast<const T*>(reinterpret_cast<const char*>(zx) + at));
-  };
   const T d = act ? dinv[g] : T(0);
   T rg = act ? b[g] : T(0);
   T xg = T(0);
+  // s0, s1 <- their sums over all rows, and the columns' z in zl; false when a
+  // wait gave up
+  const auto exchange = [&](T z, double& s0, double& s1) -> bool {
+    ++tag;
+    if (nblk == 1) {
+      zl[threadIdx.x] = z;
+      group_sum2<kCN>(s0, s1, red);
+      return true;
+    }
+    if (act) put_tagged<T>(zx + (int64_t)g * KW, z, tag);
+    grid_put2<kCN>(s0, s1, tag, nblk, slots, red);
+    int lost = 0;
+    for (int j0 = threadIdx.x; j0 < nl; j0 += kBatch * kCT) {
+      Tagged<T> w[kBatch];
+      const uint64_t* from[kBatch];
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        from[i] = zx + (int64_t)mine[min(j0 + i * kCT, nl - 1)] * KW;
+        w[i].load(from[i]);
+      }
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) zl[min(j0 + i * kCT, nl - 1)] = w[i].get(from[i], tag, lost);
+    }
+    return grid_get2<kCN>(s0, s1, tag, nblk, slots, red, lost);
+  };
   bool ok = true;
   if (neumann) {
     double s = (double)rg, s1 = 0.0;
@@ -90,11 +123,10 @@ __global__ __launch_bounds__(kCT)
   }
   T pg = d * rg;
   double rho = (double)rg * (double)pg, unused = 0.0;
-  if (act) store_shared(zx + g, pg);
-  if (ok) ok = grid_sum2<kCN>(rho, unused, ++tag, nblk, slots, red);
+  if (ok) ok = exchange(pg, rho, unused);
   if (ok && rho > 0.0 && finite(rho)) {
 #pragma unroll
-    for (int j = 0; j < kCW; ++j) pn[j] = z_at(c[j]);
+    for (int j = 0; j < kCW; ++j) pn[j] = zl[c[j]];
     for (int it = 0; it < iters; ++it) {
       T w = T(0);
 #pragma unroll
@@ -108,15 +140,14 @@ __global__ __launch_bounds__(kCT)
       if (it + 1 == iters) break;
       rg -= a * (w - mw);
       const T zg = d * rg;
-      if (act) store_shared(zx + g, zg);
       double rr = (double)rg * (double)rg, rz = rr * (double)d;
-      if (!(ok = grid_sum2<kCN>(rr, rz, ++tag, nblk, slots, red))) break;
+      if (!(ok = exchange(zg, rr, rz))) break;
       if (!finite(rr)) break;
       const T bt = (T)(rz / rho);
       rho = rz;
       pg = zg + bt * pg;
 #pragma unroll
-      for (int j = 0; j < kCW; ++j) pn[j] = z_at(c[j]) + bt * pn[j];
+      for (int j = 0; j < kCW; ++j) pn[j] = zl[c[j]] + bt * pn[j];
     }
   }
   if (act) x[g] = ok ? xg : (T)__builtin_nan("");
@@ -193,12 +224,33 @@ sem_status setup_coarse(CoarseDev& C, const sem_mesh* m, const int64_t* gid,
   if (!coarse_pattern(hn, nL, col, cseg, cperm)) return SEM_OK;
   const size_t nv = (size_t)(nf * kCW);
   C.nblk = (int)((nf + kCT - 1) / kCT);
-  C.n_sync = (int64_t)2 * C.nblk * kGridWords * 2 + 1;  // slots as 32-bit words, and the tag
-  if ((st = put(C.col, col, s)) || (st = put(C.cseg, cseg, s)) || (st = put(C.cperm, cperm, s)) ||
+  // 32-bit words: the tag (two), the slots, up to two 64-bit words of z per row
+  C.n_sync = 2 + 2 * ((int64_t)2 * C.nblk * kGridWords + 2 * nf);
+  // every workgroup's columns, each once, and the places of its rows' columns
+  // in that list; one workgroup has the rows themselves
+  std::vector<int32_t> list((size_t)C.nblk * kCT * kCW), nlist(C.nblk), place(col.size());
+  std::vector<int32_t> at(nf), in(nf, -1);
+  for (int w = 0; w < C.nblk; ++w) {
+    int n = 0;
+    const int64_t hi = std::min<int64_t>(nf, (int64_t)(w + 1) * kCT);
+    for (int64_t g = (int64_t)w * kCT; g < hi; ++g)
+      for (int j = 0; j < kCW; ++j) {
+        const int32_t cc = col[(size_t)(j * nf + g)];
+        if (in[cc] != w) {
+          in[cc] = w;
+          list[(size_t)w * kCT * kCW + n] = cc;
+          at[cc] = C.nblk == 1 ? cc : n;
+          ++n;
+        }
+        place[(size_t)(j * nf + g)] = at[cc];
+      }
+    nlist[w] = n;
+  }
+  if ((st = put(C.place, place, s)) || (st = put(C.list, list, s)) ||
+      (st = put(C.nlist, nlist, s)) || (st = put(C.cseg, cseg, s)) || (st = put(C.cperm, cperm, s)) ||
       (st = C.v64.ensure(nv * sizeof(double))) || (st = C.v32.ensure(nv * sizeof(float))) ||
       (st = C.u.ensure((size_t)nL * sizeof(double))) ||
       (st = C.w.ensure((size_t)(8 * nL) * sizeof(double))) ||
-      (st = C.zx.ensure((size_t)nf * sizeof(double))) ||
       (st = C.sync.ensure((size_t)C.n_sync * sizeof(int32_t))))
     return st;
   SEM_HIP(hipStreamSynchronize(s));  // host vectors go out of scope
@@ -239,10 +291,11 @@ sem_status coarse_cg(CoarseDev& C, const sem_mesh* m, const T* dinv, const T* b,
   const T* val = nullptr;
   if constexpr (sizeof(T) == 8) val = C.v64.as<double>();
   else val = C.v32.as<float>();
+  uint64_t* const slots = C.sync.as<uint64_t>() + 1;
   hipLaunchKernelGGL((k_coarse_cg<T>), dim3(C.nblk), dim3(kCT), 0, s, (int)m->n_free, val,
-                     C.col.as<int32_t>(), dinv, b, x, C.zx.as<T>(), iters, neumann ? 1 : 0,
-                     1.0 / (double)m->n_free, C.sync.as<uint64_t>(),
-                     C.sync.as<uint32_t>() + (C.n_sync - 1), outer);
+                     C.place.as<int32_t>(), C.list.as<int32_t>(), C.nlist.as<int32_t>(), dinv, b, x, slots + (int64_t)2 * C.nblk * kGridWords,
+                     iters, neumann ? 1 : 0, 1.0 / (double)m->n_free, slots,
+                     C.sync.as<uint32_t>(), outer);
   SEM_CHECK_LAUNCH("coarse CG");
   return SEM_OK;
 }

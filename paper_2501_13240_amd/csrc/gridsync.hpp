@@ -5,9 +5,7 @@
 // iterations instead of ending at each reduction.  Every reduction is then
 // one exchange between the workgroups: each publishes its partial sums in a
 // slot of its own, and every workgroup reads all slots and adds them in the
-// same fixed order, so all obtain bit-identical totals.  The exchange also
-// orders memory: what a workgroup stored with store_shared() before it is
-// read by load_shared() after it.
+// same fixed order, so all obtain bit-identical totals.
 //
 // A slot word is (tag << 32 | 32 bits of a double): a reader that finds the
 // tag of the exchange it waits for has the data with it, so one store and
@@ -35,16 +33,6 @@ __device__ __forceinline__ uint64_t grid_load(const uint64_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void grid_store(uint64_t* p, uint64_t v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// data exchanged between workgroups inside the kernel
-template <typename T>
-__device__ __forceinline__ T load_shared(const T* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <typename T>
-__device__ __forceinline__ void store_shared(T* p, T v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -122,15 +110,10 @@ __device__ __forceinline__ bool grid_get2(double& a, double& b, uint32_t tag, in
   return true;
 }
 
-// a, b <- their sums over all workgroups; also a barrier between them that
-// orders store_shared() before load_shared().
+// a, b <- their sums over all workgroups
 template <int NW>
 __device__ __forceinline__ bool grid_sum2(double& a, double& b, uint32_t tag, int nblk,
                                           uint64_t* __restrict__ slots, double* red) {
-  // this wavefront's shared stores have reached the device's memory before
-  // the workgroup publishes
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_s_waitcnt(0);
   grid_put2<NW>(a, b, tag, nblk, slots, red);
   return grid_get2<NW>(a, b, tag, nblk, slots, red, 0);
 }

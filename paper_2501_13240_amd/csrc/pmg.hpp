@@ -24,8 +24,8 @@ struct CoarseDev {
   bool valid = false;      // the matrix of (k == NULL, h2) is there
   double h2 = 0.0;
   int nblk = 0;
-  int64_t n_sync = 0;      // 32-bit words of `sync`: exchange slots, then the running tag
-  DevBuf col, cseg, cperm, v64, v32, u, w, zx, sync;
+  int64_t n_sync = 0;      // 32-bit words of `sync`: running tag, exchange slots, tagged z
+  DevBuf place, list, nlist, cseg, cperm, v64, v32, u, w, sync;
 };
 
 struct PmgLevel {
