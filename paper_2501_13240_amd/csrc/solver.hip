@@ -1359,7 +1359,11 @@ sem_status cg_solve(const sem_mesh* m, SolveWork& W, const CgArgs<T, Tp>& a, CgR
   chunk = std::max(1, std::min(chunk, std::max(a.max_it, 1)));
   // Small problems are launch-bound: capture one chunk of iterations as a HIP
   // graph (the iteration index lives on the device, so the same graph serves
-  // every chunk) and replay it.
+  // every chunk) and replay it.  Not with a multigrid preconditioner (the one
+  // that asks for short chunks): its iterations, some 70 launches, run no
+  // faster from a graph, and capturing them costs more than it could save (512
+  // elements, N = 7: 531 us an iteration and 890 us a solve beside them
+  // replayed, 517 and 398 us launched; 240 elements 443 and 848, 411 and 443).
   hipGraphExec_t gexec = nullptr;
   struct GraphGuard {
     hipGraphExec_t* g;
@@ -1367,7 +1371,7 @@ sem_status cg_solve(const sem_mesh* m, SolveWork& W, const CgArgs<T, Tp>& a, CgR
       if (*g) (void)hipGraphExecDestroy(*g);
     }
   } gguard{&gexec};
-  if (!a.profile && nf <= graph_max_free() && a.max_it > 0) {
+  if (!a.profile && nf <= graph_max_free() && a.max_it > 0 && a.max_chunk >= 16) {
     hipStream_t cs;
     if ((st = W.capture_stream(&cs))) return st;
     SEM_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
