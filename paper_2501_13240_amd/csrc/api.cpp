@@ -1050,7 +1050,7 @@ sem_status sem_setup_pmg(sem_mesh* m, const sem_mesh_desc* desc, const sem_pmg_o
       for (int j = 0; j < nc; ++j) JT[(size_t)j * nf + i] = J[(size_t)i * nc + j];
     std::vector<float> J32(J.begin(), J.end()), JT32(JT.begin(), JT.end());
     if ((st = upload(L.J64, J, s)) || (st = upload(L.JT64, JT, s)) || (st = upload(L.J32, J32, s)) ||
-        (st = upload(L.JT32, JT32, s)))
+        (st = upload(L.JT32, JT32, s)) || (st = setup_transfers(L, P->lv[l + 1], s)))
       return st;
   }
   SEM_HIP(hipStreamSynchronize(s));

@@ -9,7 +9,8 @@
 // interpolates element blocks (tensor product of the 1-D interpolation J_l)
 // and averages the copies of each fine node, P_l^T divides each fine value by
 // its number of copies, applies J_l^T per element and sums the copies of each
-// coarse node.  Every launch returns at once when the enclosing flexible CG
+// coarse node (on conforming meshes both through a node's first copy alone, which
+// is the same: k_transfer).  Every launch returns at once when the enclosing flexible CG
 // has finished, so overshooting iterations cost nothing.
 #include <type_traits>
 
@@ -76,6 +77,116 @@ __global__ __launch_bounds__(kInterpThreads) void interp_kernel(
     T s = T(0);
     for (int k = 0; k < n_in; ++k) s += sM[c * n_in + k] * A[k * n2 + ba];
     out[e * p_out + o] = s;
+  }
+}
+
+// The same transfers where the copies of a fine node interpolate to one value
+// (a conforming mesh, checked at the set-up), one wavefront per element and
+// sizes known at compile time.  Only a node's first copy (omap, else -1) takes
+// part: PROLONG adds the interpolated value to x there (x: the free vector of
+// the fine level), the restriction reads the residual there and counts it as
+// zero at the other copies, whose interpolation weights are the same.  Bound by
+// the fine level's map and gathers.  32x32x16 elements, FP32, N = 7 -> 3 and 3
+// -> 1: prolongation 17 and 8 us (with every copy stored, then averaged: 88
+// together), restriction 13 and 6 us (every copy read and divided by their
+// number: 55 together).
+template <typename T, int NI, int NO, bool PROLONG>
+__global__ __launch_bounds__(64) void k_transfer(const T* __restrict__ M, const T* __restrict__ in,
+                                                 const int32_t* __restrict__ map_in,
+                                                 const int32_t* __restrict__ omap,
+                                                 T* __restrict__ out,
+                                                 const int32_t* __restrict__ skip) {
+  if (skip && *skip) return;
+  constexpr int PI = NI * NI * NI, PO = NO * NO * NO, S1 = NI * NI * NO, S2 = NI * NO * NO;
+  constexpr int QI = (PI + 63) / 64, QO = (PO + 63) / 64;
+  __shared__ T sM[NO * NI];
+  __shared__ T A[PI > S2 ? PI : S2];
+  __shared__ T B[S1];
+  const int64_t e = blockIdx.x;
+  const int t = threadIdx.x;
+  int32_t gi[QI], go[QO];
+  T xo[QO];
+  const int32_t* mi = (PROLONG ? map_in : omap) + e * PI;
+#pragma unroll
+  for (int a = 0; a < QI; ++a) gi[a] = t + 64 * a < PI ? mi[t + 64 * a] : -1;
+  if constexpr (PROLONG) {
+#pragma unroll
+    for (int a = 0; a < QO; ++a) go[a] = t + 64 * a < PO ? omap[e * PO + t + 64 * a] : -1;
+  }
+  for (int a = t; a < NO * NI; a += 64) sM[a] = M[a];
+  T v[QI];
+#pragma unroll
+  for (int a = 0; a < QI; ++a) v[a] = gi[a] >= 0 ? in[gi[a]] : T(0);
+  if constexpr (PROLONG) {
+#pragma unroll
+    for (int a = 0; a < QO; ++a) xo[a] = go[a] >= 0 ? out[go[a]] : T(0);
+  }
+#pragma unroll
+  for (int a = 0; a < QI; ++a)
+    if (t + 64 * a < PI) A[t + 64 * a] = v[a];
+  __syncthreads();
+#pragma unroll
+  for (int o = t; o < S1; o += 64) {  // along i
+    const int a = o % NO, kj = o / NO;
+    T s = T(0);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) s += sM[a * NI + i] * A[kj * NI + i];
+    B[o] = s;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int o = t; o < S2; o += 64) {  // along j
+    const int a = o % NO, b = (o / NO) % NO, k = o / (NO * NO);
+    T s = T(0);
+#pragma unroll
+    for (int j = 0; j < NI; ++j) s += sM[b * NI + j] * B[(k * NI + j) * NO + a];
+    A[o] = s;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < QO; ++q) {  // along k
+    const int o = t + 64 * q;
+    if (o >= PO) break;
+    const int ba = o % (NO * NO), c = o / (NO * NO);
+    T s = T(0);
+#pragma unroll
+    for (int k = 0; k < NI; ++k) s += sM[c * NI + k] * A[k * NO * NO + ba];
+    if constexpr (PROLONG) {
+      if (go[q] >= 0) out[go[q]] = xo[q] + s;
+    } else {
+      out[e * PO + o] = s;
+    }
+  }
+}
+
+// omap[q] = the free node of local point q where q is its first copy, else -1
+__global__ void k_first_copies(int64_t nL, const int32_t* __restrict__ lmap,
+                               const int32_t* __restrict__ seg, const int32_t* __restrict__ perm,
+                               int32_t* __restrict__ omap) {
+  GRID_STRIDE(q, nL) {
+    const int32_t g = lmap[q];
+    omap[q] = g >= 0 && perm[seg[g]] == (int32_t)q ? g : -1;
+  }
+}
+
+// some values in [-1, 1] without a pattern in the node number
+__global__ void k_scatter_values(int64_t n, double* __restrict__ x) {
+  GRID_STRIDE(g, n) {
+    uint32_t h = (uint32_t)g * 2654435761u;
+    h ^= h >> 15;
+    h *= 2246822519u;
+    h ^= h >> 13;
+    x[g] = (double)(int32_t)h * (1.0 / 2147483648.0);
+  }
+}
+
+// counts copies whose value is not that of their node's first copy
+__global__ void k_copies_differ(int64_t nL, const int32_t* __restrict__ lmap,
+                                const int32_t* __restrict__ seg, const int32_t* __restrict__ perm,
+                                const double* __restrict__ vL, int* __restrict__ count) {
+  GRID_STRIDE(q, nL) {
+    const int32_t g = lmap[q];
+    if (g >= 0 && !(fabs(vL[q] - vL[perm[seg[g]]]) <= 1e-10)) atomicAdd(count, 1);
   }
 }
 
@@ -178,25 +289,26 @@ T* local_scratch(const sem_mesh* m) {
 }
 
 // The additive Schwarz sum fused with the Chebyshev recurrence: q = sum of
-// the box copies of free node g (q = S r_k), then FIRST: d = ca q, z = d;
-// else d = ca d + cb q, z += d.  q itself is never stored.
-template <typename T, bool FIRST>
+// the box copies of free node g (q = S r_k), then at STEP 0 d = ca q, later
+// d = ca d + cb q, and z = d_0 + d_1 at step 1 (neither z nor, at step 0, its
+// store is needed before), z += d from step 2 on.  `add`: z += all of them
+// (z holds the iterate that the smoothing corrects).  LAST: d is not kept.
+// Bound by its stream, of which the copies' indices are as much as the copies:
+// 29-33 us a step (average of the two smoothing levels of 32x32x16 elements, N =
+// 7).  Four steps and the correction pass 12 vectors instead of 17.
+template <typename T, int STEP, bool LAST>
 __global__ void k_schw_sum_cheb(int64_t nf, const int32_t* __restrict__ seg,
                                 const int32_t* __restrict__ perm, const T* __restrict__ box,
-                                T* __restrict__ d, T* __restrict__ z, T ca, T cb,
+                                T* __restrict__ d, T* __restrict__ z, T ca, T cb, bool add,
                                 const int32_t* __restrict__ skip) {
   if (skip && *skip) return;
   GRID_STRIDE(g, nf) {
+    const T d0 = STEP > 0 ? d[g] : T(0);
+    const T z0 = (STEP > 1 || ((STEP == 1 || LAST) && add)) ? z[g] : T(0);
     const T q = segment_sum<T>(perm, box, seg[g], seg[g + 1]);
-    if constexpr (FIRST) {
-      const T dg = ca * q;
-      d[g] = dg;
-      z[g] = dg;
-    } else {
-      const T dg = ca * d[g] + cb * q;
-      d[g] = dg;
-      z[g] += dg;
-    }
+    const T dg = STEP > 0 ? ca * d0 + cb * q : ca * q;
+    if constexpr (!LAST) d[g] = dg;
+    if constexpr (STEP > 0 || LAST) z[g] = z0 + (STEP == 1 ? d0 + dg : dg);
   }
 }
 
@@ -260,11 +372,12 @@ sem_status schwarz_apply(const PmgLevel& L, const T* r, T* z, const int32_t* ski
   return SEM_OK;
 }
 
-// z = p_m(S A) S r with the fourth-kind coefficients (as the Jacobi version).
+// z = p_m(S A) S r (add: z += it) with the fourth-kind coefficients (as the
+// Jacobi version).
 // Each Schwarz sum carries the recurrence's d and z update (k_schw_sum_cheb),
 // and the first residual r_1 = r - A d_0 is formed from r directly.
 template <typename T>
-sem_status cheb_schwarz(Pmg& P, PmgLevel& L, const T* r, T* z, const CgScalars* outer,
+sem_status cheb_schwarz(Pmg& P, PmgLevel& L, const T* r, T* z, bool add, const CgScalars* outer,
                         hipStream_t s, int* applies) {
   const sem_mesh* m = L.m;
   const int64_t nf = m->n_free;
@@ -280,30 +393,71 @@ sem_status cheb_schwarz(Pmg& P, PmgLevel& L, const T* r, T* z, const CgScalars* 
   const int32_t* xseg = L.sch.xseg.as<int32_t>();
   const int32_t* xperm = L.sch.xperm.as<int32_t>();
   sem_status st;
+  auto sum = [&](int k, double ca, double cb) {
+    const bool last = k + 1 == P.smooth_order;
+#define SEM_SUM(STEP, LAST)                                                                       \
+  hipLaunchKernelGGL((k_schw_sum_cheb<T, STEP, LAST>), dim3(grid_for(nf)), dim3(kVecBlock), 0, s, \
+                     nf, xseg, xperm, box, d, z, (T)ca, (T)cb, add, skip)
+    if (k == 0 && last) SEM_SUM(0, true);
+    else if (k == 0) SEM_SUM(0, false);
+    else if (k == 1 && last) SEM_SUM(1, true);
+    else if (k == 1) SEM_SUM(1, false);
+    else if (last) SEM_SUM(2, true);
+    else SEM_SUM(2, false);
+#undef SEM_SUM
+  };
   SEM_HIP(launch_fdm<T>(L.sch, m->E, r, box, skip, s));
-  hipLaunchKernelGGL((k_schw_sum_cheb<T, true>), dim3(grid_for(nf)), dim3(kVecBlock), 0, s, nf,
-                     xseg, xperm, box, d, z, (T)(4.0 / (3.0 * lmax)), T(0), skip);
+  sum(0, 4.0 / (3.0 * lmax), 0.0);
   for (int k = 1; k < P.smooth_order; ++k) {
     if ((st = level_residual<T>(P, L, op, d, r, rk, k == 1, skip, s))) return st;
     if (applies) ++*applies;
     SEM_HIP(launch_fdm<T>(L.sch, m->E, rk, box, skip, s));
-    const double ca = (2.0 * k - 1.0) / (2.0 * k + 3.0);
-    const double cb = (8.0 * k + 4.0) / ((2.0 * k + 3.0) * lmax);
-    hipLaunchKernelGGL((k_schw_sum_cheb<T, false>), dim3(grid_for(nf)), dim3(kVecBlock), 0, s, nf,
-                       xseg, xperm, box, d, z, (T)ca, (T)cb, skip);
+    sum(k, (2.0 * k - 1.0) / (2.0 * k + 3.0), (8.0 * k + 4.0) / ((2.0 * k + 3.0) * lmax));
   }
   SEM_CHECK_LAUNCH("Chebyshev-Schwarz");
   return SEM_OK;
 }
 
+// z = the smoothing of r, or z += it (scratch: a free vector for that)
 template <typename T>
-sem_status smooth(Pmg& P, PmgLevel& L, const T* r, T* z, const CgScalars* outer, hipStream_t s,
-                  int* applies) {
-  if (P.smoother == 1) return cheb_schwarz<T>(P, L, r, z, outer, s, applies);
+sem_status smooth(Pmg& P, PmgLevel& L, const T* r, T* z, T* scratch, bool add,
+                  const CgScalars* outer, hipStream_t s, int* applies) {
+  if (P.smoother == 1) return cheb_schwarz<T>(P, L, r, z, add, outer, s, applies);
   ChebCg c;
   c.skip_sc = outer;
-  return cheb_apply_dev<T, T>(L.m, *L.m->work, op_of<T>(L), dinv_of<T>(L), r, z, P.smooth_order,
-                              L.rho_hat, c, s, applies);
+  sem_status st = cheb_apply_dev<T, T>(L.m, *L.m->work, op_of<T>(L), dinv_of<T>(L), r,
+                                       add ? scratch : z, P.smooth_order, L.rho_hat, c, s, applies);
+  if (st || !add) return st;
+  hipLaunchKernelGGL((k_vadd<T>), dim3(grid_for(L.m->n_free)), dim3(kVecBlock), 0, s,
+                     L.m->n_free, z, scratch, outer ? &outer->done : nullptr);
+  SEM_CHECK_LAUNCH("post-smoothing");
+  return SEM_OK;
+}
+
+// The single-wavefront transfers between a level of nf^3 points per element and
+// one of nc^3; false for pairs of sizes that the default hierarchies do not
+// have (k_transfer is compiled for theirs).
+template <typename T, bool PROLONG>
+bool launch_transfer(int64_t E, int nf, int nc, const T* M, const T* in, const int32_t* map_in,
+                     const int32_t* omap, T* out, const int32_t* skip, hipStream_t s) {
+#define SEM_PAIR(F, C)                                                                          \
+  case 16 * F + C:                                                                              \
+    hipLaunchKernelGGL((k_transfer<T, (PROLONG ? C : F), (PROLONG ? F : C), PROLONG>),          \
+                       dim3((unsigned)E), dim3(64), 0, s, M, in, map_in, omap, out, skip);      \
+    return true
+  switch (16 * nf + nc) {
+    SEM_PAIR(11, 6);
+    SEM_PAIR(10, 5);
+    SEM_PAIR(9, 5);
+    SEM_PAIR(8, 4);
+    SEM_PAIR(7, 4);
+    SEM_PAIR(6, 3);
+    SEM_PAIR(5, 3);
+    SEM_PAIR(4, 2);
+    SEM_PAIR(3, 2);
+    default: return false;
+  }
+#undef SEM_PAIR
 }
 
 template <typename T>
@@ -334,7 +488,7 @@ sem_status vcycle(Pmg& P, int l, const T* r, T* x, const CgScalars* outer, hipSt
   ops.skip = skip;
   sem_status st;
   // pre-smoothing
-  if ((st = smooth<T>(P, L, r, x, outer, s, applies))) return st;
+  if ((st = smooth<T>(P, L, r, x, u, false, outer, s, applies))) return st;
   // t = r - A x, restricted to the next level
   if ((st = level_residual<T>(P, L, ops, x, r, t, true, skip, s))) return st;
   if (applies) ++*applies;
@@ -344,24 +498,28 @@ sem_status vcycle(Pmg& P, int l, const T* r, T* x, const CgScalars* outer, hipSt
   T* rc = P.vec<T>(C, 0);
   T* xc = P.vec<T>(C, 1);
   if (!cL || !rc || !xc) return fail(SEM_ENOMEM, "multigrid work space");
-  SEM_HIP(launch_interp<T>(m->E, m->n1, mc->n1, mat<T>(L.JT64, L.JT32), 2, t,
-                           m->lmap.as<int32_t>(), m->fseg.as<int32_t>(), cL, skip, s));
+  const int32_t* omap = L.omap.as<int32_t>();
+  if (!L.conforming || !launch_transfer<T, false>(m->E, m->n1, mc->n1, mat<T>(L.JT64, L.JT32), t,
+                                                  nullptr, omap, cL, skip, s))
+    SEM_HIP(launch_interp<T>(m->E, m->n1, mc->n1, mat<T>(L.JT64, L.JT32), 2, t,
+                             m->lmap.as<int32_t>(), m->fseg.as<int32_t>(), cL, skip, s));
   hipLaunchKernelGGL((k_seg_sum<T>), dim3(grid_for(mc->n_free)), dim3(kVecBlock), 0, s,
                      mc->n_free, mc->fseg.as<int32_t>(), mc->fperm.as<int32_t>(), cL, rc, skip);
   SEM_CHECK_LAUNCH("restriction");
   if ((st = vcycle<T>(P, l + 1, rc, xc, outer, s, nullptr))) return st;
   // x += P x_c
-  SEM_HIP(launch_interp<T>(m->E, mc->n1, m->n1, mat<T>(L.J64, L.J32), 1, xc,
-                           mc->lmap.as<int32_t>(), nullptr, wL, skip, s));
-  hipLaunchKernelGGL((k_seg_add_avg<T>), dim3(grid_for(nf)), dim3(kVecBlock), 0, s, nf,
-                     m->fseg.as<int32_t>(), m->fperm.as<int32_t>(), wL, x, skip);
+  if (!L.conforming || !launch_transfer<T, true>(m->E, m->n1, mc->n1, mat<T>(L.J64, L.J32), xc,
+                                                 mc->lmap.as<int32_t>(), omap, x, skip, s)) {
+    SEM_HIP(launch_interp<T>(m->E, mc->n1, m->n1, mat<T>(L.J64, L.J32), 1, xc,
+                             mc->lmap.as<int32_t>(), nullptr, wL, skip, s));
+    hipLaunchKernelGGL((k_seg_add_avg<T>), dim3(grid_for(nf)), dim3(kVecBlock), 0, s, nf,
+                       m->fseg.as<int32_t>(), m->fperm.as<int32_t>(), wL, x, skip);
+  }
   SEM_CHECK_LAUNCH("prolongation");
   // post-smoothing on t = r - A x
   if ((st = level_residual<T>(P, L, ops, x, r, t, true, skip, s))) return st;
   if (applies) ++*applies;
-  if ((st = smooth<T>(P, L, t, u, outer, s, applies))) return st;
-  hipLaunchKernelGGL((k_vadd<T>), dim3(grid_for(nf)), dim3(kVecBlock), 0, s, nf, x, u, skip);
-  SEM_CHECK_LAUNCH("post-smoothing");
+  if ((st = smooth<T>(P, L, t, x, u, true, outer, s, applies))) return st;
   return SEM_OK;
 }
 
@@ -377,6 +535,37 @@ T* Pmg::vec(PmgLevel& L, int which) {
 }
 template double* Pmg::vec<double>(PmgLevel&, int);
 template float* Pmg::vec<float>(PmgLevel&, int);
+
+sem_status setup_transfers(PmgLevel& L, const PmgLevel& C, hipStream_t s) {
+  const sem_mesh* m = L.m;
+  const sem_mesh* mc = C.m;
+  L.conforming = false;
+  if (m->nL < 1 || m->nL > INT32_MAX) return SEM_OK;
+  sem_status st = L.omap.ensure((size_t)m->nL * sizeof(int32_t));
+  DevBuf x, v, count;
+  if (st || (st = x.ensure((size_t)std::max<int64_t>(mc->n_free, 1) * sizeof(double))) ||
+      (st = v.ensure((size_t)m->nL * sizeof(double))) || (st = count.ensure(sizeof(int))))
+    return st;
+  const int32_t* lmap = m->lmap.as<int32_t>();
+  const int32_t* seg = m->fseg.as<int32_t>();
+  const int32_t* perm = m->fperm.as<int32_t>();
+  const dim3 g(grid_for(m->nL)), b(kVecBlock);
+  hipLaunchKernelGGL(k_first_copies, g, b, 0, s, m->nL, lmap, seg, perm, L.omap.as<int32_t>());
+  hipLaunchKernelGGL(k_scatter_values, dim3(grid_for(mc->n_free)), b, 0, s, mc->n_free,
+                     x.as<double>());
+  SEM_HIP(launch_fill<int>(count.as<int>(), 1, 0, s));
+  SEM_HIP(launch_interp<double>(m->E, mc->n1, m->n1, L.J64.as<double>(), 1, x.as<double>(),
+                                mc->lmap.as<int32_t>(), nullptr, v.as<double>(), nullptr, s));
+  hipLaunchKernelGGL(k_copies_differ, g, b, 0, s, m->nL, lmap, seg, perm, v.as<double>(),
+                     count.as<int>());
+  SEM_CHECK_LAUNCH("transfer set-up");
+  int n = 0;
+  SEM_HIP(hipMemcpyAsync(&n, count.p, sizeof(int), hipMemcpyDeviceToHost, s));
+  SEM_HIP(hipStreamSynchronize(s));
+  L.conforming = n == 0;
+  if (!L.conforming) L.omap.release();
+  return SEM_OK;
+}
 
 void pmg_destroy(Pmg* p) {
   if (!p) return;

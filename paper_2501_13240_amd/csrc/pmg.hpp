@@ -35,6 +35,10 @@ struct PmgLevel {
   // interpolation from level l+1 to level l, (N_l+1) x (N_{l+1}+1) row-major,
   // and its transpose (restriction), in both precisions
   DevBuf J64, J32, JT64, JT32;
+  // every copy of a node of this level interpolates to the same value, and the
+  // free node of each first copy (-1 at the others; see k_transfer)
+  bool conforming = false;
+  DevBuf omap;
   // free vectors of this level: r (input), x (output), t, u, w (scratch),
   // d, rk, q (Chebyshev-Schwarz smoothing)
   DevBuf r64, x64, t64, u64, w64, d64, k64v, q64, r32, x32, t32, u32, w32, d32, k32v, q32;
@@ -62,6 +66,8 @@ struct Pmg {
 };
 
 void pmg_destroy(Pmg* p);
+// `conforming` and `omap` of a level whose J64 to the next one, C, is there
+sem_status setup_transfers(PmgLevel& L, const PmgLevel& C, hipStream_t s);
 
 // host: 1-D Lagrange interpolation from the order-n_from GLL nodes to the
 // order-n_to GLL nodes, M is (n_to+1) x (n_from+1) row-major
