@@ -296,19 +296,47 @@ T* local_scratch(const sem_mesh* m) {
 // Bound by its stream, of which the copies' indices are as much as the copies:
 // 29-33 us a step (average of the two smoothing levels of 32x32x16 elements, N =
 // 7).  Four steps and the correction pass 12 vectors instead of 17.
+constexpr int kSumNodes = 2;  // (one node: 2-3 % more time a step)
 template <typename T, int STEP, bool LAST>
-__global__ void k_schw_sum_cheb(int64_t nf, const int32_t* __restrict__ seg,
+__global__ __launch_bounds__(kVecBlock) void k_schw_sum_cheb(int64_t nf, const int32_t* __restrict__ seg,
                                 const int32_t* __restrict__ perm, const T* __restrict__ box,
                                 T* __restrict__ d, T* __restrict__ z, T ca, T cb, bool add,
                                 const int32_t* __restrict__ skip) {
   if (skip && *skip) return;
-  GRID_STRIDE(g, nf) {
-    const T d0 = STEP > 0 ? d[g] : T(0);
-    const T z0 = (STEP > 1 || ((STEP == 1 || LAST) && add)) ? z[g] : T(0);
-    const T q = segment_sum<T>(perm, box, seg[g], seg[g + 1]);
-    const T dg = STEP > 0 ? ca * d0 + cb * q : ca * q;
+  // kSumNodes nodes at once: their chains offsets -> indices -> copies overlap
+  const int64_t n0 = (int64_t)blockIdx.x * (kSumNodes * kVecBlock) + threadIdx.x;
+  int32_t a[kSumNodes], b[kSumNodes], idx[kSumNodes][8];
+  T d0[kSumNodes], z0[kSumNodes], q[kSumNodes];
+#pragma unroll
+  for (int i = 0; i < kSumNodes; ++i) {
+    const int64_t g = n0 + i * kVecBlock;
+    const bool in = g < nf;
+    a[i] = in ? seg[g] : 0;
+    b[i] = in ? seg[g + 1] : 0;
+    d0[i] = STEP > 0 && in ? d[g] : T(0);
+    z0[i] = (STEP > 1 || ((STEP == 1 || LAST) && add)) && in ? z[g] : T(0);
+  }
+#pragma unroll
+  for (int i = 0; i < kSumNodes; ++i)
+#pragma unroll
+    for (int c = 0; c < 8; ++c) idx[i][c] = a[i] + c < b[i] ? perm[a[i] + c] : -1;
+#pragma unroll
+  for (int i = 0; i < kSumNodes; ++i) {
+    T v[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) v[c] = idx[i][c] >= 0 ? box[idx[i][c]] : T(0);
+    q[i] = T(0);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) q[i] += v[c];
+    for (int32_t c = a[i] + 8; c < b[i]; ++c) q[i] += box[perm[c]];
+  }
+#pragma unroll
+  for (int i = 0; i < kSumNodes; ++i) {
+    const int64_t g = n0 + i * kVecBlock;
+    if (g >= nf) break;
+    const T dg = STEP > 0 ? ca * d0[i] + cb * q[i] : ca * q[i];
     if constexpr (!LAST) d[g] = dg;
-    if constexpr (STEP > 0 || LAST) z[g] = z0 + (STEP == 1 ? d0 + dg : dg);
+    if constexpr (STEP > 0 || LAST) z[g] = z0[i] + (STEP == 1 ? d0[i] + dg : dg);
   }
 }
 
@@ -393,10 +421,11 @@ sem_status cheb_schwarz(Pmg& P, PmgLevel& L, const T* r, T* z, bool add, const C
   const int32_t* xseg = L.sch.xseg.as<int32_t>();
   const int32_t* xperm = L.sch.xperm.as<int32_t>();
   sem_status st;
+  const dim3 sum_grid((unsigned)((nf + kSumNodes * kVecBlock - 1) / (kSumNodes * kVecBlock)));
   auto sum = [&](int k, double ca, double cb) {
     const bool last = k + 1 == P.smooth_order;
 #define SEM_SUM(STEP, LAST)                                                                       \
-  hipLaunchKernelGGL((k_schw_sum_cheb<T, STEP, LAST>), dim3(grid_for(nf)), dim3(kVecBlock), 0, s, \
+  hipLaunchKernelGGL((k_schw_sum_cheb<T, STEP, LAST>), sum_grid, dim3(kVecBlock), 0, s,           \
                      nf, xseg, xperm, box, d, z, (T)ca, (T)cb, add, skip)
     if (k == 0 && last) SEM_SUM(0, true);
     else if (k == 0) SEM_SUM(0, false);
