@@ -310,7 +310,7 @@ struct MShape {
 // with one local copy, -(v + 2) for a shared free node v, -1 for a Dirichlet
 // copy; single-copy results go straight to the free vector wf[v], shared
 // copies' results to w (local, at the element's surface slots, for the
-// segmented sum), and epart[2 (NW e + wave) + a] receives each wavefront's sums
+// segmented sum), and epart[a E + e] receives each element's sums
 // of p w and of w over all its free copies (p = the gathered input; over the
 // copies of a shared node they add up to p_g w_g and w_g), reduced in a fixed
 // order.  MODE 3: MODE 2 with nontemporal shared-copy stores (for local arrays
@@ -467,11 +467,28 @@ __global__ __launch_bounds__((LShape<N, T>::TPB))
       st_stream(acc, w + eP + q);
     }
   }
-  // the sums of one wavefront: no barrier, no LDS
+  // the element's sums, in a fixed order; the barrier waits for LDS only, not
+  // for the stores on their way
+  if constexpr (kSums > 0) {
+    __shared__ double spw[NW][2];
 #pragma unroll
-  for (int a = 0; a < kSums; ++a) {
-    const double x = wave_sum_d(ps[a]);
-    if (lane == 0) epart[(e * NW + wv) * 2 + a] = x;
+    for (int a = 0; a < kSums; ++a) {
+      const double x = wave_sum_d(ps[a]);
+      if (lane == 0) spw[wv][a] = x;
+    }
+    if constexpr (NW > 1) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    } else {
+      __syncthreads();
+    }
+    if (t < kSums) {
+      double x = spw[0][t];
+#pragma unroll
+      for (int a = 1; a < NW; ++a) x += spw[a][t];
+      epart[(int64_t)t * gridDim.x + e] = x;
+    }
   }
 }
 
@@ -1002,8 +1019,6 @@ hipError_t run_ax_split(const sem_mesh* m, const T* u, T* wf, T* w, double* epar
   }
 }
 }  // namespace
-
-int ax_split_parts(int N, bool f64) { return has_mfma(N) ? ax_waves(N, f64 ? 8 : 4) : 0; }
 
 bool ax_split_available(const sem_mesh* m) {
   // SEM_AX_SPLIT=0 (read once) keeps the gather form in the solve

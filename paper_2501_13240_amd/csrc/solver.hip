@@ -130,25 +130,25 @@ __global__ __launch_bounds__(kVecBlock) void k_gsum_pw(int64_t nf, const int32_t
   block_partials<2>(v, part);
 }
 
-// this block's chunk of the ne partial pairs, in order (sum(w), the second
-// of a pair, serves the null-space projection only)
+// this block's chunk of the ne elements' partial sums, in order (sum(w), behind
+// the ne of p.w, serves the null-space projection only)
 __device__ __forceinline__ void epart_chunk(int64_t ne, const double* __restrict__ epart,
                                             bool mean, double (&v)[2]) {
   const int64_t lb = xcd_block(blockIdx.x, gridDim.x);
   const int64_t ch = (ne + gridDim.x - 1) / gridDim.x;
   const int64_t lo = lb * ch, hi = lo + ch < ne ? lo + ch : ne;
   for (int64_t e = lo + threadIdx.x; e < hi; e += blockDim.x) {
-    v[0] += epart[2 * e];
-    if (mean) v[1] += epart[2 * e + 1];
+    v[0] += epart[e];
+    if (mean) v[1] += epart[ne + e];
   }
 }
 
 // The same for the split operator, which has already written w at the
-// single-copy free nodes [0, n1) and the partial sums (ne pairs, one per
-// wavefront of each element: p.w and sum(w) over all its copies, p.w alone
-// without the null-space projection): segmented sums over the shared free
-// nodes [n1, nf) only, plus this block's chunk of the partial pairs (in
-// order, so the totals stay deterministic).
+// single-copy free nodes [0, n1) and the partial sums (of each of the ne
+// elements: p.w and sum(w) over all its copies, p.w alone without the
+// null-space projection): segmented sums over the shared free nodes [n1, nf)
+// only, plus this block's chunk of the partial sums (in order, so the totals
+// stay deterministic).
 template <typename T>
 __global__ __launch_bounds__(kVecBlock) void k_gsum_split_pw(
     int64_t n1, int64_t nf, const int32_t* __restrict__ seg, const int32_t* __restrict__ perm,
@@ -165,9 +165,15 @@ __global__ __launch_bounds__(kVecBlock) void k_gsum_split_pw(
   block_partials<2>(v, part);
 }
 
-// The partial pairs alone (the split Jacobi iteration, whose residual update
-// sums the shared nodes' copies itself), on a grid of kEpartBlocks
+// The partial sums alone (the split Jacobi iteration, whose residual update
+// sums the shared nodes' copies itself), on a grid of kEpartBlocks.  Up to
+// kEpartDirect sums (two an element with the null-space projection) every block
+// of the residual update adds them all itself, which saves the launch.  Whole
+// iteration, N = 7, us, this launch -> none: 512 elements 18.2 -> 15.9,
+// 1024 23.3 -> 20.9, 2048 32.1 -> 30.3, 4096 47.4 -> 46.2, but with
+// the projection 49.6 -> 51.2, and 8192 81.4 -> 82.4.
 constexpr int kEpartBlocks = 64;
+constexpr int64_t kEpartDirect = 4096;
 __global__ __launch_bounds__(kVecBlock) void k_epart_sum(int64_t ne,
                                                          const double* __restrict__ epart,
                                                          double* __restrict__ part,
@@ -204,12 +210,25 @@ __device__ __forceinline__ bool aligned16(const void* a, const void* b, const vo
 // progress (the iteration index lives on the device, so a captured chunk of
 // iterations can be replayed: only later kernels advance it).  False on a
 // breakdown (p.w <= 0 or not finite), which ends the solve.
+// EPART: part_in holds the operator's sums themselves (nblk elements).
+template <bool EPART = false>
 __device__ __forceinline__ bool cg_alpha(const double* __restrict__ part_in, int nblk,
                                          CgScalars* __restrict__ sc, double* __restrict__ ahist,
                                          bool set_pending, double& alpha, double& mw) {
   const int kit = sc->it;
   double S[2];
-  block_total<2>(part_in, nblk, S);
+  if constexpr (EPART) {
+    double one[1];
+    block_total<1>(part_in, nblk, one);
+    S[0] = one[0];
+    S[1] = 0.0;
+    if (sc->neumann) {
+      block_total<1>(part_in + nblk, nblk, one);
+      S[1] = one[0];
+    }
+  } else {
+    block_total<2>(part_in, nblk, S);
+  }
   const double pw = S[0];
   mw = sc->neumann ? S[1] * sc->inv_n : 0.0;
   if (!(pw > 0.0) || !finite(pw)) {  // same decision in every block
@@ -300,7 +319,8 @@ __global__ __launch_bounds__(kVecBlock) void k_update(int64_t nf, T* __restrict_
 // over the copies at their surface slots (seg, perm into wL) at the shared
 // nodes [n1, nf), which the iteration then never stores.  Each block takes
 // one chunk of either range, so the gathers spread over the whole grid.
-template <typename T>
+// EPART: alpha from the operator's sums of the nblk elements (kEpartDirect).
+template <typename T, bool EPART>
 __global__ __launch_bounds__(kVecBlock) void k_update_split(
     int64_t n1, int64_t nf, const int32_t* __restrict__ seg, const int32_t* __restrict__ perm,
     const T* __restrict__ wL, T* __restrict__ r, const T* __restrict__ w,
@@ -319,9 +339,11 @@ __global__ __launch_bounds__(kVecBlock) void k_update_split(
       pw[j] = w[g];
     }
   }
+  // the previous iteration's direction update has completed
+  if (EPART && blockIdx.x == 0 && threadIdx.x == 0) sc->pending = 0;
   if (sc->done) return;
   double alpha, mw;
-  if (!cg_alpha(part_in, nblk, sc, ahist, true, alpha, mw)) return;
+  if (!cg_alpha<EPART>(part_in, nblk, sc, ahist, true, alpha, mw)) return;
   const T a = (T)alpha, mwt = (T)mw;
   double v[2] = {0.0, 0.0};
   auto point = [&](int64_t g, T d, T rz, T wg) {
@@ -1201,7 +1223,7 @@ sem_status cg_solve(const sem_mesh* m, SolveWork& W, const CgArgs<T, Tp>& a, CgR
   double* partC = part + 2 * kReduceBlocks * kMaxReduce;
   // single-copy free nodes leave the operator directly (see launch_ax_split)
   const bool split = op_it.lp == 0 && ax_split_available(m);
-  const int64_t nparts = split ? m->E * ax_split_parts(m->N, sizeof(T) == 8) : 0;
+  const int64_t nparts = split ? m->E : 0;
   double* epart = split ? W.vec<double>(W.epart, 2 * nparts) : nullptr;
   if (split && !epart) return fail(SEM_ENOMEM, "work space");
   // Chebyshev fused into the iteration's kernels (needs the split operator)
@@ -1264,15 +1286,21 @@ sem_status cg_solve(const sem_mesh* m, SolveWork& W, const CgArgs<T, Tp>& a, CgR
   auto iteration = [&](hipStream_t ss) -> sem_status {
     sem_status e;
     if (split && jac) {
-      // the segmented sum folded into the residual update; the operator's
-      // sums reduced by a grid of kEpartBlocks (a short head reduction for
-      // every block of the update)
+      // the segmented sum folded into the residual update; on large meshes the
+      // operator's sums reduced by a grid of kEpartBlocks before (a short head
+      // reduction for every block of the update)
       if ((e = apply_op<T>(m, W, op_it, p, wL, ss, a.profile, w, epart, a.neumann))) return e;
-      hipLaunchKernelGGL(k_epart_sum, dim3(kEpartBlocks), dim3(kVecBlock), 0, ss, nparts, epart,
-                         partA, sc);
-      hipLaunchKernelGGL((k_update_split<T>), dim3(nb), dim3(kVecBlock), 0, ss, m->n_single, nf,
-                         m->fseg.as<int32_t>(), m->fperm2.as<int32_t>(), wL, r, w, a.dinv, partA,
-                         kEpartBlocks, partB, sc, ahist);
+      if (nparts * (a.neumann ? 2 : 1) <= kEpartDirect) {
+        hipLaunchKernelGGL((k_update_split<T, true>), dim3(nb), dim3(kVecBlock), 0, ss, m->n_single,
+                           nf, m->fseg.as<int32_t>(), m->fperm2.as<int32_t>(), wL, r, w, a.dinv,
+                           epart, (int)nparts, partB, sc, ahist);
+      } else {
+        hipLaunchKernelGGL(k_epart_sum, dim3(kEpartBlocks), dim3(kVecBlock), 0, ss, nparts, epart,
+                           partA, sc);
+        hipLaunchKernelGGL((k_update_split<T, false>), dim3(nb), dim3(kVecBlock), 0, ss,
+                           m->n_single, nf, m->fseg.as<int32_t>(), m->fperm2.as<int32_t>(), wL, r,
+                           w, a.dinv, partA, kEpartBlocks, partB, sc, ahist);
+      }
       hipLaunchKernelGGL((k_pupdate_jac<T, true>), dim3(nb), dim3(kVecBlock), 0, ss, nf, p, x, r,
                          a.dinv, partB, (int)nb, sc, hist, bhist);
       SEM_CHECK_LAUNCH("CG iteration");
