@@ -34,7 +34,10 @@
  *   - `stream` is a hipStream_t (NULL = the default stream).  Calls enqueue
  *     work on it and return without waiting unless documented as blocking.
  *     A mesh handle is used from one stream at a time (its work space is
- *     per handle).
+ *     per handle).  Solves of small meshes and coarsest multigrid levels run in
+ *     kernels whose workgroups wait for each other; each takes at most a quarter
+ *     of the chip, for HIP's default of four hardware queues.  A wait that is
+ *     not answered within seconds ends the solve with an error.
  *   - Errors: every call returns a sem_status; on SEM_EINVAL nothing was
  *     written.  sem_last_error() returns a thread-local message describing
  *     the last non-OK status of the calling thread.  HIP runtime failures
@@ -142,8 +145,9 @@ typedef struct {
                            residual (MIXED_IR) */
   double time_ms;       /* wall time of the solve on the stream (HIP events) */
   double lmax;          /* Chebyshev bound used (0 for Jacobi) */
-  double ax_ms;         /* profile = 1: summed duration of FP64 operator kernels */
-  int32_t ax_launches;  /* profile = 1: number of FP64 operator kernels timed */
+  double ax_ms;         /* profile = 1: summed duration of FP64 operator kernels (of the
+                           operator phases, where a small solve runs in one kernel) */
+  int32_t ax_launches;  /* profile = 1: number of FP64 operator kernels (phases) timed */
   int32_t pad_;
 } sem_solve_stats;
 
@@ -429,7 +433,8 @@ sem_status sem_advect_fields(const sem_mesh* mesh, int32_t rule, const void* u, 
  *                               all free nodes (default from N = 5: single-copy
  *                               nodes written by the operator directly);
  *   SEM_GRAPH_MAX_FREE=n        largest solve (free nodes) that replays
- *                               captured iteration graphs (default 262144);
+ *                               captured iteration graphs, or, on a few hundred
+ *                               elements, runs in one kernel (default 262144);
  *   SEM_AX_NT_BYTES=n           read at sem_setup_mesh: inside sem_pcg_solve
  *                               the operator stores shared-copy results with
  *                               nontemporal stores when the local array

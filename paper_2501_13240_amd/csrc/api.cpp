@@ -767,24 +767,27 @@ sem_status sem_setup_mesh(const sem_mesh_desc* desc, void* stream, sem_mesh** ou
       (st = m->B32.ensure((size_t)nL * sizeof(float))))
     return st;
   {
-    DevBuf dxyz, dbad;
-    if ((st = dxyz.ensure((size_t)3 * nL * sizeof(double))) ||
-        (st = dbad.ensure(2 * sizeof(int))) ||
-        (st = m->geo.ensure((size_t)E * 21 * sizeof(double))))
-      return st;
+    DevBuf dxyz;  // coordinates, the straight-edged form's coefficients, two flags
+    if ((st = dxyz.ensure((size_t)(3 * nL + 21 * E + 1) * sizeof(double)))) return st;
+    double* const geo = dxyz.as<double>() + 3 * nL;
+    int* const dbad = reinterpret_cast<int*>(geo + 21 * E);
     SEM_HIP(hipMemcpyAsync(dxyz.p, desc->xyz, (size_t)3 * nL * sizeof(double),
                            hipMemcpyHostToDevice, s));
-    SEM_HIP(launch_fill<int>(dbad.as<int>(), 2, 0, s));
+    SEM_HIP(launch_fill<int>(dbad, 2, 0, s));
     SEM_HIP(launch_geometry(m.get(), dxyz.as<double>(), m->G64.as<double>(), m->B64.as<double>(),
-                            m->G32.as<float>(), m->B32.as<float>(), dbad.as<int>(), s));
-    SEM_HIP(launch_straight(m.get(), dxyz.as<double>(), m->geo.as<double>(), dbad.as<int>() + 1,
-                            s));
+                            m->G32.as<float>(), m->B32.as<float>(), dbad, s));
+    SEM_HIP(launch_straight(m.get(), dxyz.as<double>(), geo, dbad + 1, s));
     int flags[2] = {0, 0};
-    SEM_HIP(hipMemcpyAsync(flags, dbad.p, sizeof(flags), hipMemcpyDeviceToHost, s));
+    SEM_HIP(hipMemcpyAsync(flags, dbad, sizeof(flags), hipMemcpyDeviceToHost, s));
     SEM_HIP(hipStreamSynchronize(s));
     const int bad = flags[0];
     m->straight = flags[1] == 0;
-    if (!m->straight) m->geo.release();
+    if (m->straight) {
+      if ((st = m->geo.ensure((size_t)E * 21 * sizeof(double)))) return st;
+      SEM_HIP(hipMemcpyAsync(m->geo.p, geo, (size_t)E * 21 * sizeof(double),
+                             hipMemcpyDeviceToDevice, s));
+      SEM_HIP(hipStreamSynchronize(s));
+    }
     if (bad > 0)
       return fail(SEM_EINVAL, "element map is not orientation-preserving (detJ <= 0) at " +
                                   std::to_string(bad) + " points");
@@ -1050,9 +1053,10 @@ sem_status sem_setup_pmg(sem_mesh* m, const sem_mesh_desc* desc, const sem_pmg_o
       for (int j = 0; j < nc; ++j) JT[(size_t)j * nf + i] = J[(size_t)i * nc + j];
     std::vector<float> J32(J.begin(), J.end()), JT32(JT.begin(), JT.end());
     if ((st = upload(L.J64, J, s)) || (st = upload(L.JT64, JT, s)) || (st = upload(L.J32, J32, s)) ||
-        (st = upload(L.JT32, JT32, s)) || (st = setup_transfers(L, P->lv[l + 1], s)))
+        (st = upload(L.JT32, JT32, s)))
       return st;
   }
+  if ((st = setup_transfers(*P, s))) return st;
   SEM_HIP(hipStreamSynchronize(s));
   pmg_destroy(m->pmg);
   m->pmg = P.release();
@@ -1176,29 +1180,33 @@ sem_status sem_setup_advection(sem_mesh* m, const sem_mesh_desc* desc, int32_t r
   const std::vector<float> eo32(eo.begin(), eo.end());
   if ((st = upload(R->mats64, mats, s)) || (st = upload(R->pts64, pts, s)) ||
       (st = upload(R->eo64, eo, s)) || (st = upload(R->eo32, eo32, s)) ||
-      (st = R->geo.ensure((size_t)m->E * 21 * sizeof(double))) ||
       (st = R->G64.ensure((size_t)m->E * 9 * Q * sizeof(double))) ||
       (st = R->G32.ensure((size_t)m->E * 9 * Q * sizeof(float))))
     return st;
-  DevBuf dxyz, dw, dbad;
-  if ((st = dxyz.ensure((size_t)3 * m->nL * sizeof(double))) || (st = upload(dw, w, s)) ||
-      (st = dbad.ensure(2 * sizeof(int))))
-    return st;
+  DevBuf dxyz;  // coordinates, the straight-edged form's coefficients, two flags
+  if ((st = dxyz.ensure((size_t)(3 * m->nL + 21 * m->E + 1) * sizeof(double)))) return st;
+  double* const geo = dxyz.as<double>() + 3 * m->nL;
+  int* const dbad = reinterpret_cast<int*>(geo + 21 * m->E);
   SEM_HIP(hipMemcpyAsync(dxyz.p, desc->xyz, (size_t)3 * m->nL * sizeof(double),
                          hipMemcpyHostToDevice, s));
-  SEM_HIP(launch_fill<int>(dbad.as<int>(), 2, 0, s));
-  SEM_HIP(launch_straight(m, dxyz.as<double>(), R->geo.as<double>(), dbad.as<int>() + 1, s));
-  SEM_HIP(launch_adv_geometry(m, q1, R->mats64.as<double>(), dw.as<double>(),
-                              dxyz.as<double>(), R->G64.as<double>(), R->G32.as<float>(),
-                              dbad.as<int>(), s));
+  SEM_HIP(launch_fill<int>(dbad, 2, 0, s));
+  SEM_HIP(launch_straight(m, dxyz.as<double>(), geo, dbad + 1, s));
+  SEM_HIP(launch_adv_geometry(m, q1, R->mats64.as<double>(), R->pts64.as<double>() + q1,
+                              dxyz.as<double>(), R->G64.as<double>(), R->G32.as<float>(), dbad,
+                              s));
   int flags[2] = {0, 0};
-  SEM_HIP(hipMemcpyAsync(flags, dbad.p, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
+  SEM_HIP(hipMemcpyAsync(flags, dbad, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
   SEM_HIP(hipStreamSynchronize(s));
   if (flags[0] > 0)
     return fail(SEM_EINVAL, "element map is not orientation-preserving (detJ <= 0) at " +
                                 std::to_string(flags[0]) + " quadrature points");
   R->straight = flags[1] == 0;
-  if (!R->straight) R->geo.release();
+  if (R->straight) {
+    if ((st = R->geo.ensure((size_t)m->E * 21 * sizeof(double)))) return st;
+    SEM_HIP(hipMemcpyAsync(R->geo.p, geo, (size_t)m->E * 21 * sizeof(double),
+                           hipMemcpyDeviceToDevice, s));
+    SEM_HIP(hipStreamSynchronize(s));
+  }
   delete m->adv[rule];
   m->adv[rule] = R.release();
   return SEM_OK;

@@ -21,7 +21,7 @@
 //
 // For larger N the scalar contractions make the kernel LDS-bound (each
 // point reads 2 (N+1) values per direction per phase from LDS).  There the
-// contractions run on the matrix cores instead (ax_mfma_kernel): each
+// contractions run on the matrix cores instead (ax_line_kernel): each
 // direction is a batch of 16-column tiles C = D X (or D^T X) with X gathered
 // from the element block in LDS, 16x16x4 MFMAs in FP64 or FP32, so every LDS
 // value feeds a whole tile column instead of one output.
@@ -31,8 +31,8 @@
 //
 // Inside the CG (N >= 5) the matrix-core kernel also splits its output: the
 // nodes with a single local copy are finished by the element itself, so it
-// stores w there straight into the free vector (with the p.w, w, p sums of
-// the iteration's dot products), and only the shared copies go through the
+// stores w there straight into the free vector (with the sums of p w, and
+// with a null space of w, over its copies), and only the shared copies go through the
 // segmented sum, from the element's surface slots.
 #include <cstdlib>
 #include <cstring>
@@ -315,7 +315,7 @@ struct MShape {
 // copies of a shared node they add up to p_g w_g and w_g), reduced in a fixed
 // order.  MODE 3: MODE 2 with nontemporal shared-copy stores (for local arrays
 // larger than the memory-side cache).  MODE 4 / 5: MODE 2 / 3 without the
-// wavefront sums (a Chebyshev pass needs none).  MODE 6 / 7: MODE 2 / 3 with
+// sums (a Chebyshev pass needs none).  MODE 6 / 7: MODE 2 / 3 with
 // p w only (sum(w) serves the null-space projection alone).
 //
 // GEO 0: factors from G and B.  GEO 1 (every element of the mesh is straight-

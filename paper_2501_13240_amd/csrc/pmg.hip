@@ -565,34 +565,45 @@ T* Pmg::vec(PmgLevel& L, int which) {
 template double* Pmg::vec<double>(PmgLevel&, int);
 template float* Pmg::vec<float>(PmgLevel&, int);
 
-sem_status setup_transfers(PmgLevel& L, const PmgLevel& C, hipStream_t s) {
-  const sem_mesh* m = L.m;
-  const sem_mesh* mc = C.m;
-  L.conforming = false;
-  if (m->nL < 1 || m->nL > INT32_MAX) return SEM_OK;
-  sem_status st = L.omap.ensure((size_t)m->nL * sizeof(int32_t));
-  DevBuf x, v, count;
-  if (st || (st = x.ensure((size_t)std::max<int64_t>(mc->n_free, 1) * sizeof(double))) ||
-      (st = v.ensure((size_t)m->nL * sizeof(double))) || (st = count.ensure(sizeof(int))))
-    return st;
-  const int32_t* lmap = m->lmap.as<int32_t>();
-  const int32_t* seg = m->fseg.as<int32_t>();
-  const int32_t* perm = m->fperm.as<int32_t>();
-  const dim3 g(grid_for(m->nL)), b(kVecBlock);
-  hipLaunchKernelGGL(k_first_copies, g, b, 0, s, m->nL, lmap, seg, perm, L.omap.as<int32_t>());
-  hipLaunchKernelGGL(k_scatter_values, dim3(grid_for(mc->n_free)), b, 0, s, mc->n_free,
-                     x.as<double>());
-  SEM_HIP(launch_fill<int>(count.as<int>(), 1, 0, s));
-  SEM_HIP(launch_interp<double>(m->E, mc->n1, m->n1, L.J64.as<double>(), 1, x.as<double>(),
-                                mc->lmap.as<int32_t>(), nullptr, v.as<double>(), nullptr, s));
-  hipLaunchKernelGGL(k_copies_differ, g, b, 0, s, m->nL, lmap, seg, perm, v.as<double>(),
-                     count.as<int>());
-  SEM_CHECK_LAUNCH("transfer set-up");
-  int n = 0;
-  SEM_HIP(hipMemcpyAsync(&n, count.p, sizeof(int), hipMemcpyDeviceToHost, s));
+sem_status setup_transfers(Pmg& P, hipStream_t s) {
+  const int nt = (int)P.lv.size() - 1;
+  if (nt < 1) return SEM_OK;
+  // scratch of all levels at once: a count per level, coarse values, copies
+  int64_t n_xc = 1, n_v = 1;
+  for (int l = 0; l < nt; ++l) {
+    n_xc = std::max(n_xc, P.lv[l + 1].m->n_free);
+    n_v = std::max(n_v, P.lv[l].m->nL);
+  }
+  DevBuf tmp;
+  sem_status st = tmp.ensure((size_t)(nt + n_xc + n_v) * sizeof(double));
+  if (st) return st;
+  int* const count = tmp.as<int>();
+  double* const x = tmp.as<double>() + nt;
+  double* const v = x + n_xc;
+  SEM_HIP(launch_fill<int>(count, nt, 0, s));
+  for (int l = 0; l < nt; ++l) {
+    PmgLevel& L = P.lv[l];
+    const sem_mesh* m = L.m;
+    const sem_mesh* mc = P.lv[l + 1].m;
+    if ((st = L.omap.ensure((size_t)std::max<int64_t>(m->nL, 1) * sizeof(int32_t)))) return st;
+    const int32_t* lmap = m->lmap.as<int32_t>();
+    const int32_t* seg = m->fseg.as<int32_t>();
+    const int32_t* perm = m->fperm.as<int32_t>();
+    const dim3 g(grid_for(m->nL)), b(kVecBlock);
+    hipLaunchKernelGGL(k_first_copies, g, b, 0, s, m->nL, lmap, seg, perm, L.omap.as<int32_t>());
+    hipLaunchKernelGGL(k_scatter_values, dim3(grid_for(mc->n_free)), b, 0, s, mc->n_free, x);
+    SEM_HIP(launch_interp<double>(m->E, mc->n1, m->n1, L.J64.as<double>(), 1, x,
+                                  mc->lmap.as<int32_t>(), nullptr, v, nullptr, s));
+    hipLaunchKernelGGL(k_copies_differ, g, b, 0, s, m->nL, lmap, seg, perm, v, count + l);
+    SEM_CHECK_LAUNCH("transfer set-up");
+  }
+  std::vector<int> n(nt);
+  SEM_HIP(hipMemcpyAsync(n.data(), count, nt * sizeof(int), hipMemcpyDeviceToHost, s));
   SEM_HIP(hipStreamSynchronize(s));
-  L.conforming = n == 0;
-  if (!L.conforming) L.omap.release();
+  for (int l = 0; l < nt; ++l) {
+    P.lv[l].conforming = n[l] == 0;
+    if (n[l]) P.lv[l].omap.release();
+  }
   return SEM_OK;
 }
 

@@ -66,8 +66,9 @@ struct Pmg {
 };
 
 void pmg_destroy(Pmg* p);
-// `conforming` and `omap` of a level whose J64 to the next one, C, is there
-sem_status setup_transfers(PmgLevel& L, const PmgLevel& C, hipStream_t s);
+// `conforming` and `omap` of every level but the coarsest (meshes and J64 are
+// there); blocks
+sem_status setup_transfers(Pmg& P, hipStream_t s);
 
 // host: 1-D Lagrange interpolation from the order-n_from GLL nodes to the
 // order-n_to GLL nodes, M is (n_to+1) x (n_from+1) row-major
