@@ -333,7 +333,7 @@ def mixed_vs_fp64(sem, only="", reps=20):
 
 def pmg_cube_iteration_bytes(nel=32, orders=(9, 4, 2, 1), smooth_order=4, coarse_iters=30):
     """Algorithmic HBM bytes of one iteration of FP64 flexible CG preconditioned
-    by one FP32 Schwarz-smoothed V-cycle on the all-Neumann nel^3 cube (every
+    by one FP32 Schwarz-smoothed V-cycle (smooth_order >= 3) on the all-Neumann nel^3 cube (every
     kernel the iteration launches, each array counted once per access; index
     arrays 4 B, FP32 values 4 B, FP64 values 8 B).  Returns (total, per-kernel
     dict of bytes per iteration).  Counts of the structured mesh:
@@ -369,16 +369,20 @@ def pmg_cube_iteration_bytes(nel=32, orders=(9, 4, 2, 1), smooth_order=4, coarse
     for lev, N in enumerate(orders):
         nL, nf, n1, bp, bc = sizes(N)
         if lev == len(orders) - 1:
-            # coarsest: fixed Jacobi-PCG iterations (operator 32 B per local point,
-            # sum 8 B per copy + 12 per node, update 20 B and p update 16 B per node)
-            add("coarse CG", coarse_iters * (32.0 * nL + 8.0 * nL + 12.0 * nf + 36.0 * nf))
+            # coarsest: one resident kernel (27 matrix values and places a row, then
+            # 16 B a row and iteration handed between its workgroups)
+            add("coarse CG", 27 * 8.0 * nf + coarse_iters * 16.0 * nf)
             break
         m = smooth_order
         add("ax FP32 (32 B per local point)", (2 * (m - 1) + 2) * 32.0 * nL)
         add("Schwarz local solves (12 B per box point + factors)",
             2 * m * E * (12.0 * bp + 4.0 * (3 * (N + 3) ** 2 + 3 * (N + 3))))
-        add("Schwarz sums with the recurrence (8 B per box copy + 12 / 20 B per node)",
-            2 * (8.0 * bc + 12.0 * nf) + 2 * (m - 1) * (8.0 * bc + 20.0 * nf))
+        # per node: offsets 4 B; d written at the first step, read at the last, both
+        # between; z written at the second and read and written from the third on
+        # (post-smoothing adds into the iterate: read at the second too)
+        node = [8.0] + [16.0] + [20.0] * (m - 3) + [16.0]
+        add("Schwarz sums with the recurrence (8 B per box copy + 8 to 20 B per node)",
+            2 * m * 8.0 * bc + (2 * sum(node) + 4.0) * nf)
         if N >= 5:
             # split-form residual: wf and r (or b) at single-copy nodes, 8 B per
             # shared copy, 8 B per shared node, r written
@@ -389,13 +393,11 @@ def pmg_cube_iteration_bytes(nel=32, orders=(9, 4, 2, 1), smooth_order=4, coarse
             add("residual sums (8 B per local copy + 12 B per node)",
                 (2 * (m - 1) + 2) * (8.0 * nL + 12.0 * nf))
         nLc, nfc = sizes(orders[lev + 1])[:2]
-        add("restriction (4 B per fine point, 8 per fine node, 4 per coarse point; then 8 B "
-            "per coarse copy + 8 per coarse node)",
-            4.0 * nL + 8.0 * nf + 4.0 * nLc + 8.0 * nLc + 8.0 * nfc)
-        add("prolongation (4 B per coarse point and node, 4 per fine point; then 8 B per "
-            "copy + 12 per node)",
-            4.0 * nLc + 4.0 * nfc + 4.0 * nL + 8.0 * nL + 12.0 * nf)
-        add("post-smoothing add (12 B per node)", 12.0 * nf)
+        add("restriction (4 B per fine point and node, 4 per coarse point; then 8 B per "
+            "coarse copy + 8 per coarse node)",
+            4.0 * nL + 4.0 * nf + 4.0 * nLc + 8.0 * nLc + 8.0 * nfc)
+        add("prolongation (4 B per coarse point and node, 4 per fine point, 8 per fine node)",
+            4.0 * nLc + 4.0 * nfc + 4.0 * nL + 8.0 * nf)
     return sum(out.values()), out
 
 

@@ -116,34 +116,30 @@ __global__ __launch_bounds__(kGeoThreads) void straight_kernel(const double* __r
   const double* x = xyz + e * 3 * P;
   double c[8][3];  // 1, r, s, t, rs, rt, st, rst
   double size = 0.0;
+#pragma unroll
   for (int d = 0; d < 3; ++d) {
-    double X[2][2][2];
-    for (int k = 0; k < 2; ++k)
-      for (int j = 0; j < 2; ++j)
-        for (int i = 0; i < 2; ++i) {
-          X[k][j][i] = x[3 * (k * h * P2 + j * h * n1 + i * h) + d];
-          size = fmax(size, fabs(X[k][j][i]));
-        }
-    double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int k = 0; k < 2; ++k)
-      for (int j = 0; j < 2; ++j)
-        for (int i = 0; i < 2; ++i) {
-          const double r = i ? 1.0 : -1.0, q = j ? 1.0 : -1.0, t = k ? 1.0 : -1.0, v = X[k][j][i];
-          s[0] += v;
-          s[1] += r * v;
-          s[2] += q * v;
-          s[3] += t * v;
-          s[4] += r * q * v;
-          s[5] += r * t * v;
-          s[6] += q * t * v;
-          s[7] += r * q * t * v;
-        }
-    for (int a = 0; a < 8; ++a) c[a][d] = 0.125 * s[a];
+    double v[8];  // corners, i fastest
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      v[q] = x[3 * ((q >> 2) * h * P2 + ((q >> 1) & 1) * h * n1 + (q & 1) * h) + d];
+      size = fmax(size, fabs(v[q]));
+    }
+#pragma unroll
+    for (int a = 0; a < 8; ++a) {
+      // signs of the corners: r, s, t where the coefficient has them
+      const int m = a == 0 ? 0 : a == 1 ? 1 : a == 2 ? 2 : a == 3 ? 4 : a == 4 ? 3 : a == 5 ? 5
+                    : a == 6 ? 6 : 7;
+      double s = 0.0;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) s += (__builtin_popcount(m & ~q) & 1) ? -v[q] : v[q];
+      c[a][d] = 0.125 * s;
+    }
   }
   const double tol = 8.0 * 2.220446049250313e-16 * size;
   int off = 0;
   for (int q = threadIdx.x; q < P; q += blockDim.x) {
     const double r = xi[q % n1], s = xi[(q / n1) % n1], t = xi[q / P2];
+#pragma unroll
     for (int d = 0; d < 3; ++d) {
       const double v = c[0][d] + r * c[1][d] + s * c[2][d] + t * c[3][d] + r * s * c[4][d] +
                        r * t * c[5][d] + s * t * c[6][d] + r * s * t * c[7][d];
@@ -151,7 +147,9 @@ __global__ __launch_bounds__(kGeoThreads) void straight_kernel(const double* __r
     }
   }
   if (__syncthreads_or(off) && threadIdx.x == 0) atomicAdd(curved, 1);
-  if (threadIdx.x < 21) geo[e * 21 + threadIdx.x] = c[1 + threadIdx.x / 3][threadIdx.x % 3];
+  if (threadIdx.x == 0)
+#pragma unroll
+    for (int a = 0; a < 21; ++a) geo[e * 21 + a] = c[1 + a / 3][a % 3];
 }
 
 }  // namespace
