@@ -233,22 +233,57 @@ __global__ void k_seg_dec(int64_t nf, const int32_t* __restrict__ seg,
 // The same residuals from the split operator's output (levels of order >= 5
 // that carry its routing): w at the single-copy nodes [0, n1) is read from
 // wf, contiguous; only the shared nodes [n1, nf) sum their copies, from the
-// elements' surface slots.  SUB: r = b - A d; else r -= A d.  Every block
-// takes a chunk of each range, so the segmented sums are spread over all.
+// elements' surface slots.  SUB: r = b - A d; else r -= A d.  A thread takes
+// kResSingle nodes of the first range and kResShared of the second: the shared
+// nodes' chains (offsets, copy indices, copies) overlap each other and the
+// first range's stream.  FP32, 32x32x16 elements, N = 7: 30.3 us (a chunk of each
+// range per block, one node at a time) -> 21.1 us, 5.0 TB/s; 24^3 elements, N = 9:
+// 45.3 -> 31.5 us.
+constexpr int kResSingle = 4, kResShared = 2;
 template <typename T, bool SUB>
 __global__ __launch_bounds__(kVecBlock) void k_split_res(
     int64_t n1, int64_t nf, const int32_t* __restrict__ seg, const int32_t* __restrict__ perm,
     const T* __restrict__ wf, const T* __restrict__ wL, const T* __restrict__ b,
     T* __restrict__ r, const int32_t* __restrict__ skip) {
   if (skip && *skip) return;
-  {
-    BLOCK_CHUNK(g, n1) r[g] = (SUB ? b[g] : r[g]) - wf[g];
+  const int64_t g1 = (int64_t)blockIdx.x * (kResSingle * kVecBlock) + threadIdx.x;
+  const int64_t g2 = n1 + (int64_t)blockIdx.x * (kResShared * kVecBlock) + threadIdx.x;
+  int32_t lo[kResShared], hi[kResShared], idx[kResShared][8];
+  T rs[kResShared], r1[kResSingle], w1[kResSingle];
+#pragma unroll
+  for (int i = 0; i < kResShared; ++i) {
+    const int64_t g = g2 + i * kVecBlock;
+    const bool in = g < nf;
+    lo[i] = in ? seg[g] : 0;
+    hi[i] = in ? seg[g + 1] : 0;
+    rs[i] = in ? (SUB ? b[g] : r[g]) : T(0);
   }
-  {
-    BLOCK_CHUNK(i, nf - n1) {
-      const int64_t g = n1 + i;
-      r[g] = (SUB ? b[g] : r[g]) - segment_sum<T>(perm, wL, seg[g], seg[g + 1]);
-    }
+#pragma unroll
+  for (int i = 0; i < kResSingle; ++i) {
+    const int64_t g = g1 + i * kVecBlock;
+    const bool in = g < n1;
+    r1[i] = in ? (SUB ? b[g] : r[g]) : T(0);
+    w1[i] = in ? wf[g] : T(0);
+  }
+#pragma unroll
+  for (int i = 0; i < kResShared; ++i)
+#pragma unroll
+    for (int c = 0; c < 8; ++c) idx[i][c] = lo[i] + c < hi[i] ? perm[lo[i] + c] : -1;
+#pragma unroll
+  for (int i = 0; i < kResSingle; ++i) {
+    const int64_t g = g1 + i * kVecBlock;
+    if (g < n1) r[g] = r1[i] - w1[i];
+  }
+#pragma unroll
+  for (int i = 0; i < kResShared; ++i) {
+    const int64_t g = g2 + i * kVecBlock;
+    T v[8], sum = T(0);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) v[c] = idx[i][c] >= 0 ? wL[idx[i][c]] : T(0);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) sum += v[c];
+    for (int32_t c = lo[i] + 8; c < hi[i]; ++c) sum += wL[perm[c]];
+    if (g < nf) r[g] = rs[i] - sum;
   }
 }
 
@@ -296,7 +331,7 @@ T* local_scratch(const sem_mesh* m) {
 // Bound by its stream, of which the copies' indices are as much as the copies:
 // 29-33 us a step (average of the two smoothing levels of 32x32x16 elements, N =
 // 7).  Four steps and the correction pass 12 vectors instead of 17.
-constexpr int kSumNodes = 2;  // (one node: 2-3 % more time a step)
+constexpr int kSumNodes = 2;  // (one: 5-9 % more time, four: 6-12 %; N = 7 and 9)
 template <typename T, int STEP, bool LAST>
 __global__ __launch_bounds__(kVecBlock) void k_schw_sum_cheb(int64_t nf, const int32_t* __restrict__ seg,
                                 const int32_t* __restrict__ perm, const T* __restrict__ box,
@@ -365,11 +400,14 @@ sem_status level_residual(Pmg& P, PmgLevel& L, const Op<T>& op, const T* d, cons
     if ((st = apply_op<T>(m, W, op, d, wL, s, false, wf, nullptr))) return st;
     const int32_t* seg = m->fseg.as<int32_t>();
     const int32_t* perm = m->fperm2.as<int32_t>();
+    const int64_t per1 = kResSingle * kVecBlock, per2 = kResShared * kVecBlock;
+    const dim3 grid((unsigned)std::max((m->n_single + per1 - 1) / per1,
+                                       (nf - m->n_single + per2 - 1) / per2));
     if (sub)
-      hipLaunchKernelGGL((k_split_res<T, true>), dim3(grid_for(nf)), dim3(kVecBlock), 0, s,
+      hipLaunchKernelGGL((k_split_res<T, true>), grid, dim3(kVecBlock), 0, s,
                          m->n_single, nf, seg, perm, wf, wL, b, r, skip);
     else
-      hipLaunchKernelGGL((k_split_res<T, false>), dim3(grid_for(nf)), dim3(kVecBlock), 0, s,
+      hipLaunchKernelGGL((k_split_res<T, false>), grid, dim3(kVecBlock), 0, s,
                          m->n_single, nf, seg, perm, wf, wL, b, r, skip);
   } else {
     if ((st = apply_op<T>(m, W, op, d, wL, s, false))) return st;
